@@ -144,6 +144,15 @@ struct GemmLaunch {
 hipError_t launch_linear(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_linear_static(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_linear_asym(const GemmLaunch& a, hipStream_t stream);
+// The same layers on the wide kernel (w4a4_wide_kernel.h: tiles of TR x 32 rows
+// by 256 columns, no split): wide_row_tiles returns the TR with which it is
+// expected to beat w4a4_linear's schedule a.sch, which it then replaces by
+// its own, or 0.
+enum class WideMode { kPlain = 0, kQuantized = 1, kStatic = 2, kAsym = 3 };
+int wide_row_tiles(GemmLaunch& a, WideMode mode);
+hipError_t launch_wide(const GemmLaunch& a, int tr, hipStream_t stream);
+hipError_t launch_wide_static(const GemmLaunch& a, int tr, hipStream_t stream);
+hipError_t launch_wide_asym(const GemmLaunch& a, int tr, hipStream_t stream);
 hipError_t launch_gemm_i32(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_gemm_conv(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_gemm_conv_static(const GemmLaunch& a, hipStream_t stream);

@@ -247,18 +247,15 @@ __device__ __forceinline__ void stage_tile_bf16(const v16f (&out)[2][2], const f
 // Outputs, K-group-major with g = column / 64: codes [g][M][32], flags
 // [g][M][64 / lzs], scales [g][M], zeros [g][M]; rows past M fall outside the
 // buffer ranges and are dropped.
-template <bool GELU>
-__device__ __forceinline__ void quantize_tile_out(const v16f (&out)[2][2], const float (&cs)[2],
-                                                  const float (&b)[2], lds_u8* tb, int lane,
-                                                  int64_t row_base, int64_t col_base, int64_t M,
+// quantize_rows_out: the same from a region that holds the bf16 tile already
+// (rows row_base .. row_base + 63, columns col_base .. col_base + 63; rows
+// from m_end on are not written).
+__device__ __forceinline__ void quantize_rows_out(lds_u8* tb, int lane, int64_t row_base,
+                                                  int64_t col_base, int64_t m_end, int64_t M,
                                                   int64_t N, const QuantOut& qout)
 {
     if (col_base >= N)
         return;                              // wave-uniform
-    stage_tile_bf16<GELU>(out, cs, b, tb, lane);
-    // the wave reads back only what it wrote itself: LDS order within the
-    // wave suffices, the clobber keeps the compiler's order
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     lds_u8* const row = tb + lane * 128;
     const uint32_t rx = (uint32_t)((lane >> 1) & 7) << 4;
     auto chunk = [&](int c) { return (lds_v4u*)(row + (((uint32_t)c << 4) ^ rx)); };
@@ -324,7 +321,7 @@ __device__ __forceinline__ void quantize_tile_out(const v16f (&out)[2][2], const
 
     const int64_t g = col_base / 64;
     const int64_t rg0 = g * M + row_base;           // (group, first row)
-    const uint32_t rows_in = (uint32_t)max((int64_t)0, min(M - row_base, (int64_t)64));
+    const uint32_t rows_in = (uint32_t)max((int64_t)0, min(m_end - row_base, (int64_t)64));
     const Rsrc rc = make_rsrc(qout.codes + rg0 * 32, rows_in * 32u);
     __builtin_amdgcn_raw_buffer_store_b128(v4u{w[0], w[1], w[2], w[3]}, rc, lane * 32, 0, 0);
     __builtin_amdgcn_raw_buffer_store_b128(v4u{w[4], w[5], w[6], w[7]}, rc, lane * 32 + 16, 0, 0);
@@ -348,6 +345,21 @@ __device__ __forceinline__ void quantize_tile_out(const v16f (&out)[2][2], const
         const Rsrc rz = make_rsrc(qout.zeros + rg0, rows_in);
         __builtin_amdgcn_raw_buffer_store_b8((uint8_t)0, rz, lane, 0, 0);
     }
+}
+
+template <bool GELU>
+__device__ __forceinline__ void quantize_tile_out(const v16f (&out)[2][2], const float (&cs)[2],
+                                                  const float (&b)[2], lds_u8* tb, int lane,
+                                                  int64_t row_base, int64_t col_base, int64_t M,
+                                                  int64_t N, const QuantOut& qout)
+{
+    if (col_base >= N)
+        return;                              // wave-uniform
+    stage_tile_bf16<GELU>(out, cs, b, tb, lane);
+    // the wave reads back only what it wrote itself: LDS order within the
+    // wave suffices, the clobber keeps the compiler's order
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    quantize_rows_out(tb, lane, row_base, col_base, M, M, N, qout);
 }
 
 // Decode roles (decode thread d = tid - 512, 0..255): A row d (32 code bytes,

@@ -34,12 +34,18 @@ int linear_resident_blocks()
 
 hipError_t launch_linear(const GemmLaunch& a, hipStream_t stream)
 {
+    GemmLaunch w = a;
+    if (const int tr = wide_row_tiles(w, a.qout.codes ? WideMode::kQuantized : WideMode::kPlain))
+        return launch_wide(w, tr, stream);
     return a.qout.codes ? launch_linear_mode<false, true>(a, stream)
                         : launch_linear_mode<false, false>(a, stream);
 }
 
 hipError_t launch_linear_static(const GemmLaunch& a, hipStream_t stream)
 {
+    GemmLaunch w = a;
+    if (const int tr = wide_row_tiles(w, WideMode::kStatic))
+        return launch_wide_static(w, tr, stream);
     return launch_linear_mode<true, false>(a, stream);
 }
 

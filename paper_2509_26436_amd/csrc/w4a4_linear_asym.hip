@@ -7,6 +7,9 @@ namespace quartz {
 
 hipError_t launch_linear_asym(const GemmLaunch& a, hipStream_t stream)
 {
+    GemmLaunch w = a;
+    if (const int tr = wide_row_tiles(w, WideMode::kAsym))
+        return launch_wide_asym(w, tr, stream);
     return launch_linear_mode<false, false, true>(a, stream);
 }
 
