@@ -144,15 +144,22 @@ struct GemmLaunch {
 hipError_t launch_linear(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_linear_static(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_linear_asym(const GemmLaunch& a, hipStream_t stream);
-// The same layers on the wide kernel (w4a4_wide_kernel.h: tiles of TR x 32 rows
-// by 256 columns, no split): wide_row_tiles returns the TR with which it is
-// expected to beat w4a4_linear's schedule a.sch, which it then replaces by
-// its own, or 0.
-enum class WideMode { kPlain = 0, kQuantized = 1, kStatic = 2, kAsym = 3 };
-int wide_row_tiles(GemmLaunch& a, WideMode mode);
-hipError_t launch_wide(const GemmLaunch& a, int tr, hipStream_t stream);
-hipError_t launch_wide_static(const GemmLaunch& a, int tr, hipStream_t stream);
-hipError_t launch_wide_asym(const GemmLaunch& a, int tr, hipStream_t stream);
+// The same layers, and the convolutions, on the wide kernel
+// (w4a4_wide_kernel.h: tiles of tr x 32 rows by wn x 32 columns, no workspace).
+// wide_shape returns the tile with which it is expected to beat
+// w4a4_linear's schedule `lin` (tr = 0: none).
+enum class WideMode { kPlain = 0, kStatic = 1, kAsym = 2 };
+struct WideShape {
+    int tr, wn;
+};
+WideShape wide_shape(int64_t M, int64_t N, int64_t K, WideMode mode, const GemmSchedule& lin,
+                     bool conv = false);
+GemmSchedule wide_schedule(const GemmLaunch& a, const WideShape& w);
+hipError_t launch_wide(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
+hipError_t launch_wide_static(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
+hipError_t launch_wide_asym(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
+hipError_t launch_wide_conv(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
+hipError_t launch_wide_conv_static(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
 hipError_t launch_gemm_i32(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_gemm_conv(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_gemm_conv_static(const GemmLaunch& a, hipStream_t stream);

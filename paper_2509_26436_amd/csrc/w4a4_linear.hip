@@ -34,18 +34,16 @@ int linear_resident_blocks()
 
 hipError_t launch_linear(const GemmLaunch& a, hipStream_t stream)
 {
-    GemmLaunch w = a;
-    if (const int tr = wide_row_tiles(w, a.qout.codes ? WideMode::kQuantized : WideMode::kPlain))
-        return launch_wide(w, tr, stream);
+    if (const WideShape w = wide_shape(a.M, a.N, a.K, WideMode::kPlain, a.sch); w.tr > 0)
+        return launch_wide(a, w, stream);
     return a.qout.codes ? launch_linear_mode<false, true>(a, stream)
                         : launch_linear_mode<false, false>(a, stream);
 }
 
 hipError_t launch_linear_static(const GemmLaunch& a, hipStream_t stream)
 {
-    GemmLaunch w = a;
-    if (const int tr = wide_row_tiles(w, WideMode::kStatic))
-        return launch_wide_static(w, tr, stream);
+    if (const WideShape w = wide_shape(a.M, a.N, a.K, WideMode::kStatic, a.sch); w.tr > 0)
+        return launch_wide_static(a, w, stream);
     return launch_linear_mode<true, false>(a, stream);
 }
 

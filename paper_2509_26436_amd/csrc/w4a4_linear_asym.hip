@@ -7,9 +7,8 @@ namespace quartz {
 
 hipError_t launch_linear_asym(const GemmLaunch& a, hipStream_t stream)
 {
-    GemmLaunch w = a;
-    if (const int tr = wide_row_tiles(w, WideMode::kAsym))
-        return launch_wide_asym(w, tr, stream);
+    if (const WideShape w = wide_shape(a.M, a.N, a.K, WideMode::kAsym, a.sch); w.tr > 0)
+        return launch_wide_asym(a, w, stream);
     return launch_linear_mode<false, false, true>(a, stream);
 }
 
