@@ -44,9 +44,6 @@ namespace quartz {
 
 namespace {
 
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-
-
 // ------------------------------------------------------------ fp8 expansion
 // One (group, row) of a K-group-major LZS activation per thread: its 32 code
 // bytes decoded to 64 e4m3 bytes at out[row][64 g ..] (word w of the group
@@ -106,13 +103,15 @@ __device__ __forceinline__ v8i load32(const uint8_t* p)
     return v8i{(int)a.x, (int)a.y, (int)a.z, (int)a.w, (int)b.x, (int)b.y, (int)b.z, (int)b.w};
 }
 
-// operand of the scale outer product (fp16 32x32x16, only k = 0 non-zero):
-// the lower half-wave supplies k = 0 .. 7, the upper one k = 8 .. 15
-__device__ __forceinline__ v8h scale_operand(uint16_t bits, int h)
+// operand of the scale outer product (fp16 32x32x8, only k = 0 non-zero); the
+// key's or channel's word is zero in the upper half-wave, which holds k = 4 ..
+__device__ __forceinline__ v16f mfma_outer(int a, int b)
 {
-    v8h v = {};
-    v[0] = h ? (_Float16)0.0f : __builtin_bit_cast(_Float16, bits);
-    return v;
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+    const v16f zero = {};
+    return __builtin_amdgcn_mfma_f32_32x32x8f16(__builtin_bit_cast(v4h, v2i{a, 0}),
+                                                __builtin_bit_cast(v4h, v2i{b, 0}), zero, 0, 0, 0);
 }
 
 __device__ __forceinline__ v16f mfma_fp8(const v8i& a, const v8i& b)
@@ -121,44 +120,49 @@ __device__ __forceinline__ v16f mfma_fp8(const v8i& a, const v8i& b)
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, zero, 0, 0, 0, 0, 0, 0);
 }
 
-__device__ __forceinline__ v16f mfma_outer(const v8h& a, const v8h& b)
+// v of this lane and of lane l ^ 32
+__device__ __forceinline__ float2 both_halves(float v)
 {
-    const v16f zero = {};
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, zero, 0, 0, 0);
-}
-
-__device__ __forceinline__ float xhalf(float v)       // value of lane l ^ 32
-{
-    return __shfl_xor(v, 32, 64);
+    const uint32_t b = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
 
 // LDS staging of one 64-key chunk, in the order the MFMA lanes read it, so
 // that every operand read is one conflict-free ds_read_b128 per 16 bytes:
 //   K~   [t][g][j][lane][16 B]: lane (rho, h) of key tile t holds bytes
-//        64 g + 32 h + 16 j .. of key kappa(t, rho) (see krow below);
+//        64 g + 32 h + 16 j .. of key kappa(t, rho) (see the header);
 //   V~^T [i][j][lane][16 B]: lane (n, h) holds bytes 32 h + 16 j .. of the
 //        chunk's 64 keys of channel 32 i + n;
-//   the key scales [t][g][rho] and the channel scales [D] (fp16).
+//   the key scales [t][g][lane] and the channel scales [i][lane]: words of an
+//   fp16 value in lanes 0 .. 31, zeros in the others.
 template <int G, int W>
 struct AttnStage {
     static constexpr int D = 64 * G;
-    static constexpr int kK = 64 * D;               // K~ bytes
-    static constexpr int kV = D * 64;               // V~^T bytes
-    static constexpr int kSk = 64 * G * 2;
-    static constexpr int kSv = D * 2;
-    static constexpr int kBytes = kK + kV + kSk + kSv;
+    static constexpr int kV = 64 * D;               // offsets: V~^T,
+    static constexpr int kSk = kV + D * 64;         // key scales,
+    static constexpr int kSv = kSk + 2 * G * 256;   // channel scales
+    static constexpr int kBytes = kSv + D * 8;
     static constexpr int kThreads = 64 * W;
-    static constexpr int kKPieces = kK / 16, kVPieces = kV / 16;   // 16-byte pieces
-    static constexpr int kKItems = (kKPieces + kThreads - 1) / kThreads;   // per thread
-    static constexpr int kVItems = (kVPieces + kThreads - 1) / kThreads;
+    static constexpr int kPieces = 4 * D;           // 16-byte pieces of K~, and of V~^T
+    static constexpr int kItems = (kPieces + kThreads - 1) / kThreads;   // per thread
 };
 
-// One block: 4 waves, queries qb * 128 + 32 w .. + 31 of head `head`, which
+// One block: W waves, queries 32 W qb + 32 w .. + 31 of head `head`, which
 // share the staged chunks.  qx / kx: [heads L][64 G] e4m3, qs / ks:
 // [G][heads L] fp16; vx: [heads d][L] e4m3 (V^T), vs: [L / 64][heads d] fp16;
 // o: bf16 [L][ldo], head h at columns h d ...
+//
+// What bounds it is the issue of vector instructions (per 64-key chunk and
+// wave 24 MFMAs at d = 128 beside ~520, 64 of them exponentials), so both
+// passes are written as slots: a slot issues the matrix product of one unit
+// (32 rows by 32 queries of one 64-group, with the outer product of its
+// scales) and multiplies out the unit before it, whose product ran meanwhile,
+// beside a piece of the softmax or of the quantizer; the operands are read
+// from LDS a slot ahead.  Pass 2 runs the PV units of the chunk before, then
+// the score units of the chunk after the one it quantizes.
 template <int GS, int G, int W>
-__global__ __launch_bounds__(64 * W, 8 / W) void lzs_attention_fused_kernel(
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void lzs_attention_fused_kernel(
     const uint8_t* __restrict__ qx, const uint16_t* __restrict__ qs,
     const uint8_t* __restrict__ kx, const uint16_t* __restrict__ ks,
     const uint8_t* __restrict__ vx, const uint16_t* __restrict__ vs, int64_t heads, int64_t L,
@@ -167,9 +171,8 @@ __global__ __launch_bounds__(64 * W, 8 / W) void lzs_attention_fused_kernel(
     using St = AttnStage<G, W>;
     constexpr int D = St::D;
     constexpr int TV = D / 32;                 // channel tiles of the PV product
+    constexpr int NU = 2 * G;                  // score units of a chunk
     __shared__ __attribute__((aligned(16))) uint8_t smem[2][St::kBytes];
-    // each wave's Q~ operand, [g][j][lane][16 B] (written and read by that wave only)
-    __shared__ __attribute__((aligned(16))) uint8_t qsm[W][G * 2048];
 
     // blocks of one head on one XCD (consecutive block ids go round robin
     // over the 8 XCDs), so its K~ / V~^T chunks are shared in that L2
@@ -178,254 +181,414 @@ __global__ __launch_bounds__(64 * W, 8 / W) void lzs_attention_fused_kernel(
     const int64_t logical = total % 8 == 0 ? (bid % 8) * (total / 8) + bid / 8 : bid;
     const int64_t head = logical / qblocks;
     const int tid = threadIdx.x;
-    const int64_t q0 = (logical % qblocks) * (32 * W) + (tid >> 6) * 32;
+    const int64_t q0 = (logical % qblocks) * (32 * W) + __builtin_amdgcn_readfirstlane(tid >> 6) * 32;
     // a wave past the end of a ragged last block still loads and waits at
     // the barriers, and computes nothing (wave-uniform)
     const bool active = q0 < L;
     const int lane = tid & 63;
     const int n = lane & 31, h = lane >> 5;
     const int64_t rows = heads * L;
-    const int64_t chunks = L / 64;
+    const int chunks = (int)(L / 64);
 
-    // ---- cooperative staging: thread tid moves pieces tid + 256 p
+    // ---- cooperative staging: thread tid moves pieces tid + 64 W p
     // K~ piece u: key u / (D / 16), bytes 16 (u % (D / 16)) of its row
-    auto k_lds_off = [](int u) {
+    auto rho_of = [](int key) { return 8 * ((key >> 2) & 3) + 4 * (key >> 5) + (key & 3); };
+    auto k_lds_off = [&](int u) {
         const int key = u / (D / 16), part = u % (D / 16);
         const int g = part >> 2, hh = (part >> 1) & 1, j = part & 1;
-        const int t = (key >> 4) & 1;
-        const int rho = 8 * ((key >> 2) & 3) + 4 * (key >> 5) + (key & 3);
-        return (((t * G + g) * 2 + j) * 64 + rho + 32 * hh) * 16;
+        return (((((key >> 4) & 1) * G + g) * 2 + j) * 64 + rho_of(key) + 32 * hh) * 16;
     };
     // V~^T piece u: channel u / 4, bytes 16 (u % 4) of its 64-key row
     auto v_lds_off = [](int u) {
         const int ch = u >> 2, part = u & 3;
-        const int i = ch >> 5, nn = ch & 31, hh = part >> 1, j = part & 1;
-        return St::kK + ((i * 2 + j) * 64 + nn + 32 * hh) * 16;
+        return St::kV + (((ch >> 5) * 2 + (part & 1)) * 64 + (ch & 31) + 32 * (part >> 1)) * 16;
     };
-    // key scale of key `key`, group g -> [t][g][rho]
-    auto sk_lds_off = [](int key, int g) {
-        const int t = (key >> 4) & 1;
-        const int rho = 8 * ((key >> 2) & 3) + 4 * (key >> 5) + (key & 3);
-        return St::kK + St::kV + ((t * G + g) * 32 + rho) * 2;
-    };
-    v4u kr[St::kKItems], vr[St::kVItems];     // native vectors: kept in registers
-    uint16_t skr = 0, svr = 0;
-    auto load_chunk = [&](int64_t c, bool with_v) {
+    v4u kr[St::kItems], vr[St::kItems];       // native vectors: kept in registers
+    uint32_t skr = 0, svr = 0;
+    auto load_k = [&](int c) {
+        c = min(c, chunks - 1);
         const uint8_t* kc = kx + (head * L + 64 * c) * D;
 #pragma unroll
-        for (int p = 0; p < St::kKItems; ++p)
-            if (tid + St::kThreads * p < St::kKPieces)
+        for (int p = 0; p < St::kItems; ++p)
+            if (tid + St::kThreads * p < St::kPieces)
                 kr[p] = reinterpret_cast<const v4u*>(kc)[tid + St::kThreads * p];
         if (tid < 64 * G)
             skr = ks[(tid >> 6) * rows + head * L + 64 * c + (tid & 63)];
-        if (with_v) {
-#pragma unroll
-            for (int p = 0; p < St::kVItems; ++p) {
-                const int u = tid + St::kThreads * p;
-                if (u < St::kVPieces)
-                    vr[p] = *reinterpret_cast<const v4u*>(vx + (head * D + (u >> 2)) * L + 64 * c + 16 * (u & 3));
-            }
-            if (tid < D)
-                svr = vs[c * heads * D + head * D + tid];
-        }
     };
-    auto store_chunk = [&](int b, bool with_v) {
+    auto load_v = [&](int c) {
+        c = min(c, chunks - 1);
+#pragma unroll
+        for (int p = 0; p < St::kItems; ++p) {
+            const int u = tid + St::kThreads * p;
+            if (u < St::kPieces)
+                vr[p] = *reinterpret_cast<const v4u*>(vx + (head * D + (u >> 2)) * L + 64 * c + 16 * (u & 3));
+        }
+        if (tid < D)
+            svr = vs[c * heads * D + head * D + tid];
+    };
+    auto store_k = [&](int b) {
         uint8_t* s = smem[b];
 #pragma unroll
-        for (int p = 0; p < St::kKItems; ++p)
-            if (tid + St::kThreads * p < St::kKPieces)
+        for (int p = 0; p < St::kItems; ++p)
+            if (tid + St::kThreads * p < St::kPieces)
                 *reinterpret_cast<v4u*>(s + k_lds_off(tid + St::kThreads * p)) = kr[p];
-        if (tid < 64 * G)
-            *reinterpret_cast<uint16_t*>(s + sk_lds_off(tid & 63, tid >> 6)) = skr;
-        if (with_v) {
-#pragma unroll
-            for (int p = 0; p < St::kVItems; ++p)
-                if (tid + St::kThreads * p < St::kVPieces)
-                    *reinterpret_cast<v4u*>(s + v_lds_off(tid + St::kThreads * p)) = vr[p];
-            if (tid < D)
-                *reinterpret_cast<uint16_t*>(s + St::kK + St::kV + St::kSk + 2 * tid) = svr;
+        if (tid < 64 * G) {
+            const int key = tid & 63;
+            *reinterpret_cast<uint32_t*>(s + St::kSk + ((((key >> 4) & 1) * G + (tid >> 6)) * 64 + rho_of(key)) * 4) = skr;
         }
     };
+    auto store_v = [&](int b) {
+        uint8_t* s = smem[b];
+#pragma unroll
+        for (int p = 0; p < St::kItems; ++p)
+            if (tid + St::kThreads * p < St::kPieces)
+                *reinterpret_cast<v4u*>(s + v_lds_off(tid + St::kThreads * p)) = vr[p];
+        if (tid < D)
+            *reinterpret_cast<uint32_t*>(s + St::kSv + ((tid >> 5) * 64 + (tid & 31)) * 4) = svr;
+    };
+    // (loads in flight stay in flight)
+    auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    // ---- what the waves share, in order: pass 1 reads chunk c from buffer
+    // c & 1 while c + 2 waits in registers to replace it; pass 2 at chunk c
+    // writes K~ of c + 2 and V~^T of c into buffer c & 1 and reads K~ of c + 1
+    // and V~^T of c - 1 from the other.
+    for (int i = tid; i < 2 * (2 * G + TV) * 32; i += St::kThreads) {   // the zeros of the scales' upper lanes
+        const int b = i / ((2 * G + TV) * 32), row = i / 32 % (2 * G + TV);
+        *reinterpret_cast<uint32_t*>(smem[b] + St::kSk + row * 256 + 128 + (i & 31) * 4) = 0;
+    }
+    auto begin1 = [&] {
+        load_k(0);
+        store_k(0);
+        load_k(1);
+        store_k(1);
+        load_k(2);
+        barrier();
+    };
+    auto refill1 = [&](int c) {                // chunk c has been read
+        store_k(c & 1);
+        load_k(c + 3);
+    };
+    auto begin2 = [&] {
+        barrier();
+        load_k(0);
+        store_k(0);
+        load_k(1);
+        load_v(0);
+        store_k(1);
+        store_v(1);                            // (stands in for chunk -1, whose codes are 0)
+        load_k(2);
+        barrier();
+    };
+    auto refill2 = [&](int c) {
+        store_k(c & 1);
+        store_v(c & 1);
+        load_k(c + 3);
+        load_v(c + 1);
+    };
+    if (!active) {
+        begin1();
+        for (int c = 0; c < chunks; ++c) {
+            barrier();
+            refill1(c);
+        }
+        begin2();
+        barrier();
+        for (int c = 0; c < chunks; ++c) {
+            refill2(c);
+            barrier();
+        }
+        return;
+    }
+
     auto lds32 = [&](const uint8_t* s) {
         const uint4 a = *reinterpret_cast<const uint4*>(s);
         const uint4 b = *reinterpret_cast<const uint4*>(s + 1024);
         return v8i{(int)a.x, (int)a.y, (int)a.z, (int)a.w, (int)b.x, (int)b.y, (int)b.z, (int)b.w};
     };
-
-    uint8_t* const qw = qsm[tid >> 6];
-    v8h sqop[G];
-    if (active) {
+    v8i qop[G];
+    int sq[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const uint4* src = reinterpret_cast<const uint4*>(qx + (head * L + q0 + n) * D + 64 * g + 32 * h);
-            *reinterpret_cast<uint4*>(qw + g * 2048 + lane * 16) = src[0];
-            *reinterpret_cast<uint4*>(qw + g * 2048 + 1024 + lane * 16) = src[1];
-            sqop[g] = scale_operand(qs[g * rows + head * L + q0 + n], h);
-        }
+    for (int g = 0; g < G; ++g) {
+        qop[g] = load32(qx + (head * L + q0 + n) * D + 64 * g + 32 * h);
+        sq[g] = qs[g * rows + head * L + q0 + n];
     }
 
-    // x (the scores before the 1 / sqrt(d)) of the chunk in stage s: x[t][r]
-    // belongs to key 32 h + 16 t + r of the chunk and query q0 + n
-    auto scores = [&](const uint8_t* s, v16f (&x)[2]) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const v8i kop = lds32(s + (t * G + g) * 2048 + lane * 16);
-                const uint16_t skb =
-                    *reinterpret_cast<const uint16_t*>(s + St::kK + St::kV + ((t * G + g) * 32 + n) * 2);
-                const v16f sc = mfma_outer(scale_operand(skb, h), sqop[g]);
-                const v16f p = mfma_fp8(kop, lds32(qw + g * 2048 + lane * 16));
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    x[t][r] = g == 0 ? p[r] * sc[r] : fmaf(p[r], sc[r], x[t][r]);
-            }
-        }
+    // score unit u = t G + g: x[t] gains group g's product
+    v8i op;                                    // the next unit's rows and their scales
+    int sc_next;
+    auto fetch_k = [&](const uint8_t* s, int u) {
+        op = lds32(s + u * 2048 + lane * 16);
+        sc_next = *reinterpret_cast<const int*>(s + St::kSk + u * 256 + lane * 4);
     };
+    auto fetch_v = [&](const uint8_t* s, int i) {
+        op = lds32(s + St::kV + i * 2048 + lane * 16);
+        sc_next = *reinterpret_cast<const int*>(s + St::kSv + i * 256 + lane * 4);
+    };
+    v16f x[2], pc, sc;                         // pc, sc: the pending unit's products
+    auto score = [&](auto uc, const v16f& p, const v16f& s) {
+        constexpr int t = decltype(uc)::value / G, g = decltype(uc)::value % G;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            x[t][r] = g == 0 ? p[r] * s[r] : fmaf(p[r], s[r], x[t][r]);
+        asm volatile("" : "+v"(x[t]));         // not sunk out of its slot
+    };
+    auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
 
-    // pass 1: per lane the running max and sum of exp over its 32 keys of
-    // every chunk, in the base-2 domain: exp(S - m) = 2^((x - m_x) kexp)
-    float m = -INFINITY, l = 0.0f;
-    load_chunk(0, false);
-    store_chunk(0, false);
-    __syncthreads();
-    for (int64_t c = 0; c < chunks; ++c) {
-        if (c + 1 < chunks)
-            load_chunk(c + 1, false);
-        if (active) {
-            v16f x[2];
-            scores(smem[c & 1], x);
-            // four independent chains per reduction (a lone chain of 32
-            // dependent instructions leaves the SIMD idle between them)
-            float cm4[4] = {x[0][0], x[0][8], x[1][0], x[1][8]};
+    // ---- pass 1: per lane the sum of e = 2^(x kexp + nf) over its 32 keys of
+    // every chunk.  -nf is an integer near the maximum of x kexp: any
+    // reference does that neither overflows nor loses the sum, so it is moved
+    // (to a tile's maximum) only when a tile's sum passes 2^12, and no maximum
+    // is formed otherwise.
+    constexpr float kMost = 4096.0f;
+    float nf = 1e30f, l = 0.0f;                // (the first tile's sum is infinite)
+    auto tile_sum = [&](auto tc) {
+        const v16f& v = x[decltype(tc)::value];
+        // four independent chains
+        auto sum = [&] {
+            float s4[4];
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int r = 0; r < 16; ++r) {
+                const float e = __builtin_amdgcn_exp2f(fmaf(v[r], kexp, nf));
+                s4[r & 3] = r < 4 ? e : s4[r & 3] + e;
+            }
+            return (s4[0] + s4[1]) + (s4[2] + s4[3]);
+        };
+        float s = sum();
+        if (__builtin_amdgcn_ballot_w64(s > kMost)) {
+            float m = v[0];
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    cm4[2 * t + r / 8] = fmaxf(cm4[2 * t + r / 8], x[t][r]);
-            const float mn = fmaxf(m, fmaxf(fmaxf(cm4[0], cm4[1]), fmaxf(cm4[2], cm4[3])));
-            const float nmk = -mn * kexp;
-            float cs4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    cs4[2 * t + r / 8] += __builtin_amdgcn_exp2f(fmaf(x[t][r], kexp, nmk));
-            l = l * __builtin_amdgcn_exp2f((m - mn) * kexp) + ((cs4[0] + cs4[1]) + (cs4[2] + cs4[3]));
-            m = mn;
+            for (int r = 1; r < 16; ++r)
+                m = fmaxf(m, v[r]);
+            const float to = s > kMost ? -__builtin_rintf(m * kexp) : nf;
+            l *= __builtin_amdgcn_exp2f(to - nf);
+            nf = to;
+            s = sum();
         }
-        if (c + 1 < chunks)
-            store_chunk((c + 1) & 1, false);
-        __syncthreads();
+        l += s;
+    };
+    begin1();
+    fetch_k(smem[0], 0);
+    pc = mfma_fp8(op, qop[0]);
+    sc = mfma_outer(sc_next, sq[0]);
+    fetch_k(smem[0], 1);
+    for (int c = 0; c < chunks; ++c) {
+        const uint8_t* const here = smem[c & 1];
+        const uint8_t* const next = smem[(c & 1) ^ 1];
+        auto slot = [&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            if constexpr (u == NU - 2)
+                barrier();                     // all of this chunk is read, the next is there
+            const v16f pn = mfma_fp8(op, qop[(u + 1) % G]);
+            const int sn = sc_next;
+            fence();
+            if constexpr (u + 2 < NU)
+                fetch_k(here, u + 2);
+            else
+                fetch_k(next, u + 2 - NU);
+            fence();
+            score(uc, pc, sc);
+            fence();
+            sc = mfma_outer(sn, sq[(u + 1) % G]);
+            pc = pn;
+            fence();
+            if constexpr (u % G == G - 1)
+                tile_sum(std::integral_constant<int, u / G>());
+            fence();
+        };
+        slot(std::integral_constant<int, 0>());
+        slot(std::integral_constant<int, 1>());
+        if constexpr (G == 2) {
+            slot(std::integral_constant<int, 2>());
+            slot(std::integral_constant<int, 3>());
+        }
+        refill1(c);
     }
     {
         // the two half-waves' keys of the same query (identical result in both)
-        const float mo = xhalf(m), lo = xhalf(l);
-        const float mf = fmaxf(m, mo);
-        l = l * __builtin_amdgcn_exp2f((m - mf) * kexp) + lo * __builtin_amdgcn_exp2f((mo - mf) * kexp);
-        m = mf;
+        const float2 n2 = both_halves(nf), l2 = both_halves(l);
+        nf = fminf(n2.x, n2.y);
+        l = l2.x * __builtin_amdgcn_exp2f(nf - n2.x) + l2.y * __builtin_amdgcn_exp2f(nf - n2.y);
     }
     const float inv_l = 1.0f / l;
-    const float nmk = -m * kexp;
 
+    // ---- pass 2
     v16f acc[TV];
 #pragma unroll
     for (int i = 0; i < TV; ++i)
         acc[i] = v16f{};
-    // pass 2
-    load_chunk(0, true);
-    store_chunk(0, true);
-    __syncthreads();
-    for (int64_t c = 0; c < chunks; ++c) {
-        if (c + 1 < chunks)
-            load_chunk(c + 1, true);
-        if (active) {
-            const uint8_t* s = smem[c & 1];
-            v16f x[2];
-            scores(s, x);
-            // e = exp(S - max) and its maximum over each 8 consecutive keys
-            float e8[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    #pragma unroll
-            for (int t = 0; t < 2; ++t)
-    #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    x[t][r] = __builtin_amdgcn_exp2f(fmaf(x[t][r], kexp, nmk));
-                    e8[2 * t + r / 8] = fmaxf(e8[2 * t + r / 8], x[t][r]);
-                }
-            // alpha = max of P = e / sum over the 64-key group (binary32 rounding
-            // of e * inv_l is monotone, so max(e) * inv_l is that maximum), the
-            // fp16 scale and r = 1 / s.  The code multiplier R = inv_l r takes
-            // P r in one rounding instead of two.
-            float emax = fmaxf(fmaxf(e8[0], e8[1]), fmaxf(e8[2], e8[3]));
-            emax = fmaxf(emax, xhalf(emax));
-            const float alpha = emax * inv_l;
-            const _Float16 s16 = (_Float16)(alpha / 127.0f);
-            const uint16_t sbits = __builtin_bit_cast(uint16_t, s16);
-            const float R = sbits == 0 ? 0.0f : inv_l * (1.0f / (float)s16);
-            // FLAG of each subgroup from its largest code (q = min(rne(e R), 127)
-            // is monotone in e), as the e4m3 table of c 2^FLAG, c = 0 .. 7: the
-            // base table with FLAG added to the exponent field of entries 1 .. 7
-            auto flag_of = [&](float emx) {
-                return lzs_flag((uint32_t)fminf(__builtin_rintf(emx * R), 127.0f));
-            };
-            int fl[4];
-            if constexpr (GS == 8) {
-    #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    fl[k] = flag_of(e8[k]);
-            } else if constexpr (GS == 16) {
-    #pragma unroll
-                for (int t = 0; t < 2; ++t)
-                    fl[2 * t] = fl[2 * t + 1] = flag_of(fmaxf(e8[2 * t], e8[2 * t + 1]));
-            } else {
-                float e4 = fmaxf(fmaxf(e8[0], e8[1]), fmaxf(e8[2], e8[3]));
-                if constexpr (GS == 64)
-                    e4 = emax;
-                fl[0] = fl[1] = fl[2] = fl[3] = flag_of(e4);
-            }
-            Fp8Table tab[4];
-    #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                tab[k].lo = kTabLo + (uint32_t)fl[k] * 0x08080800u;
-                tab[k].hi = kTabHi + (uint32_t)fl[k] * 0x08080808u;
-            }
-            // The k-slice of P~^T: dword k of the operand holds keys (relative to
-            // the half-wave) 8 (k / 2) + {0, 4, 1, 5} (k even) or {2, 6, 3, 7}
-            // (k odd), the byte order of the expanded V~^T rows.  Per dword the
-            // four Stage-1 codes q = min(rne(e R), 127) as bytes (v_cvt_pk_u8_f32
-            // rounds to nearest even), c = q >> FLAG per byte, and the e4m3 value
-            // of c 2^FLAG by table lookup.
-            v8i pop;
-    #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int t = k >> 2, base = 8 * ((k >> 1) & 1) + 2 * (k & 1);
-                const int sub = k >> 1;
-                uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(x[t][base] * R, 127.0f), 0u, 0u);
-                w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(x[t][base + 4] * R, 127.0f), 1u, w);
-                w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(x[t][base + 1] * R, 127.0f), 2u, w);
-                w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(x[t][base + 5] * R, 127.0f), 3u, w);
-                const uint32_t cb = (w >> fl[sub]) & 0x07070707u;
-                pop[k] = (int)__builtin_amdgcn_perm(tab[sub].hi, tab[sub].lo, cb);
-            }
-            const v8h spop = scale_operand(sbits, h);
-#pragma unroll
-            for (int i = 0; i < TV; ++i) {
-                const v8i vop = lds32(s + St::kK + i * 2048 + lane * 16);
-                const uint16_t svb = *reinterpret_cast<const uint16_t*>(
-                    s + St::kK + St::kV + St::kSk + (32 * i + n) * 2);
-                const v16f sc = mfma_outer(scale_operand(svb, h), spop);
-                const v16f p = mfma_fp8(vop, pop);
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[i][r] = fmaf(p[r], sc[r], acc[i][r]);
-            }
-        }
-        if (c + 1 < chunks)
-            store_chunk((c + 1) & 1, true);
-        __syncthreads();
+    begin2();
+    auto first = [&](auto uc) {                // the scores of chunk 0, the last unit left pending
+        constexpr int u = decltype(uc)::value;
+        fetch_k(smem[0], u);
+        pc = mfma_fp8(op, qop[u % G]);
+        sc = mfma_outer(sc_next, sq[u % G]);
+        if constexpr (u + 1 < NU)
+            score(uc, pc, sc);
+    };
+    first(std::integral_constant<int, 0>());
+    first(std::integral_constant<int, 1>());
+    if constexpr (G == 2) {
+        first(std::integral_constant<int, 2>());
+        first(std::integral_constant<int, 3>());
     }
-    if (!active)
-        return;
+    barrier();
+    fetch_v(smem[1], 0);
+
+    // the quantized probabilities of the chunk before (operand, group scale)
+    v8i pop = {};
+    int sp = 0;
+    v8i pnew;
+    int spnew = 0;
+    float R = 0.0f;                            // e R: the Stage-1 code before rounding
+    int fl[4] = {0, 0, 0, 0};
+    auto max8 = [&](int t, int half) {
+        const v16f& v = x[t];
+        float m = v[8 * half];
+#pragma unroll
+        for (int r = 1; r < 8; ++r)
+            m = fmaxf(m, v[8 * half + r]);
+        return m;
+    };
+    // rne(e R) in the low half (a code is 127 at most but for a group scale
+    // that was rounded down)
+    auto code_bits = [&](float v) {
+        return __float_as_uint(fmaf(__builtin_amdgcn_exp2f(fmaf(v, kexp, nf)), R, kMagic));
+    };
+    float m8[4];
+    auto group_scale_of = [&] {
+        float xm = fmaxf(fmaxf(m8[0], m8[1]), fmaxf(m8[2], m8[3]));
+        const float2 x2 = both_halves(xm);
+        xm = fmaxf(x2.x, x2.y);
+        // alpha = max of P = e / sum over the 64-key group, the fp16 scale
+        // s = alpha / 127 (the IEEE quotient: one correction step), R = 1 / (sum s)
+        const float alpha = __builtin_amdgcn_exp2f(fmaf(xm, kexp, nf)) * inv_l;
+        const float a0 = alpha * kInv127;
+        const _Float16 s16 = (_Float16)fmaf(fmaf(-127.0f, a0, alpha), kInv127, a0);
+        const uint32_t sbits = __builtin_bit_cast(uint16_t, s16);
+        const float s = (float)s16, r0 = __builtin_amdgcn_rcpf(s);
+        R = sbits == 0 ? 0.0f : inv_l * fmaf(r0, fmaf(-s, r0, 1.0f), r0);
+        spnew = (int)sbits;
+        // FLAG of each subgroup from its largest code (monotone in x)
+        auto flag_of = [&](float v) { return lzs_flag(min(code_bits(v) - kMagicBits, 127u)); };
+        if constexpr (GS == 8) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                fl[k] = flag_of(m8[k]);
+        } else if constexpr (GS == 16) {
+            fl[0] = fl[1] = flag_of(fmaxf(m8[0], m8[1]));
+            fl[2] = fl[3] = flag_of(fmaxf(m8[2], m8[3]));
+        } else {
+            const float v = GS == 64 ? xm : fmaxf(fmaxf(m8[0], m8[1]), fmaxf(m8[2], m8[3]));
+            fl[0] = fl[1] = fl[2] = fl[3] = flag_of(v);
+        }
+    };
+    // The k-slice of P~^T: dword k of the operand holds keys (relative to
+    // the half-wave) 8 (k / 2) + {0, 4, 1, 5} (k even) or {2, 6, 3, 7}
+    // (k odd), the byte order of the expanded V~^T rows.  Dwords 2 sub and
+    // 2 sub + 1: the codes in pairs, clamped to 127, as bytes, c = q >> FLAG, and the e4m3 value of
+    // c 2^FLAG by lookup in the base table with FLAG added to the exponent
+    // field of entries 1 .. 7.
+    auto quantize8 = [&](int sub) {
+        const v16f& v = x[sub >> 1];
+        uint32_t q[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            q[r] = code_bits(v[8 * (sub & 1) + r]);
+        auto pair = [](uint32_t lo, uint32_t hi) {
+            const lzs_us2 most = {127, 127};
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(
+                __builtin_bit_cast(lzs_us2, __builtin_amdgcn_perm(hi, lo, 0x05040100u)), most));
+        };
+        const uint32_t hi = kTabHi + (uint32_t)fl[sub] * 0x08080808u;
+        const uint32_t lo = kTabLo + (uint32_t)fl[sub] * 0x08080800u;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const uint32_t a = pair(q[2 * k], q[2 * k + 4]), b = pair(q[2 * k + 1], q[2 * k + 5]);
+            const uint32_t w = __builtin_amdgcn_perm(b, a, 0x06040200u);
+            pnew[2 * sub + k] = (int)__builtin_amdgcn_perm(hi, lo, (w >> fl[sub]) & 0x07070707u);
+        }
+        asm volatile("" : "+v"(pnew));
+    };
+    auto add_pv = [&](int i) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            acc[i][r] = fmaf(pc[r], sc[r], acc[i][r]);
+        asm volatile("" : "+v"(acc[i]));
+    };
+    for (int c = 0; c < chunks; ++c) {
+        const uint8_t* const there = smem[(c & 1) ^ 1];
+        refill2(c);
+        auto slot = [&](auto kc) {
+            // units: TV of PV (chunk c - 1), NU scores (chunk c + 1)
+            constexpr int k = decltype(kc)::value;
+            if constexpr (k == TV + NU - 1)
+                barrier();                     // all of `there` is read, the other buffer is there
+            v16f pn;
+            if constexpr (k < TV)
+                pn = mfma_fp8(op, pop);
+            else
+                pn = mfma_fp8(op, qop[(k - TV) % G]);
+            const int sn = sc_next;
+            fence();
+            if constexpr (k + 1 < TV)
+                fetch_v(there, k + 1);
+            else if constexpr (k + 1 < TV + NU)
+                fetch_k(there, k + 1 - TV);
+            else
+                fetch_v(smem[c & 1], 0);
+            fence();
+            if constexpr (k == 0)
+                score(std::integral_constant<int, NU - 1>(), pc, sc);
+            else if constexpr (k <= TV)
+                add_pv(k - 1);
+            else
+                score(std::integral_constant<int, k - TV - 1>(), pc, sc);
+            fence();
+            if constexpr (k < TV)
+                sc = mfma_outer(sn, sp);
+            else
+                sc = mfma_outer(sn, sq[(k - TV) % G]);
+            pc = pn;
+            fence();
+            // the quantizer: TV slots for the four pieces; x[t] is free for
+            // the next chunk's scores after its two
+            if constexpr (k == 0) {
+                m8[0] = max8(0, 0);
+                m8[1] = max8(0, 1);
+                m8[2] = max8(1, 0);
+                m8[3] = max8(1, 1);
+                group_scale_of();
+            } else if constexpr (k <= TV) {
+                constexpr int per = 4 / TV;
+#pragma unroll
+                for (int j = 0; j < per; ++j)
+                    quantize8(per * (k - 1) + j);
+            }
+            fence();
+        };
+        slot(std::integral_constant<int, 0>());
+        slot(std::integral_constant<int, 1>());
+        slot(std::integral_constant<int, 2>());
+        slot(std::integral_constant<int, 3>());
+        if constexpr (G == 2) {
+            slot(std::integral_constant<int, 4>());
+            slot(std::integral_constant<int, 5>());
+            slot(std::integral_constant<int, 6>());
+            slot(std::integral_constant<int, 7>());
+        }
+        pop = pnew;
+        sp = spnew;
+    }
+    // the PV units of the last chunk (the first one's rows are fetched)
+#pragma unroll
+    for (int i = 0; i < TV; ++i) {
+        if (i > 0)
+            fetch_v(smem[(chunks - 1) & 1], i);
+        pc = mfma_fp8(op, pop);
+        sc = mfma_outer(sc_next, sp);
+        add_pv(i);
+    }
     // O^T tile i, register r: channel 32 i + 8 (r / 4) + 4 h + r % 4 of query
     // q0 + n; four consecutive channels per 8-byte store
     typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
