@@ -130,10 +130,13 @@ __device__ __forceinline__ float2 both_halves(float v)
 
 // LDS staging of one 64-key chunk, in the order the MFMA lanes read it, so
 // that every operand read is one conflict-free ds_read_b128 per 16 bytes:
-//   K~   [t][g][j][lane][16 B]: lane (rho, h) of key tile t holds bytes
+//   K~   [t][g][j][slot][16 B]: lane (rho, h) of key tile t reads bytes
 //        64 g + 32 h + 16 j .. of key kappa(t, rho) (see the header);
-//   V~^T [i][j][lane][16 B]: lane (n, h) holds bytes 32 h + 16 j .. of the
+//   V~^T [i][j][slot][16 B]: lane (n, h) reads bytes 32 h + 16 j .. of the
 //        chunk's 64 keys of channel 32 i + n;
+//   slot = 32 h + (rho or n) ^ swz(g, h, j): 8 threads that store consecutive
+//   pieces of a row reach 8 different slots mod 8 (without it every piece of a
+//   key met in the same banks: 24 % of the kernel's cycles at L = 4608);
 //   the key scales [t][g][lane] and the channel scales [i][lane]: words of an
 //   fp16 value in lanes 0 .. 31, zeros in the others.
 template <int G, int W>
@@ -146,6 +149,10 @@ struct AttnStage {
     static constexpr int kThreads = 64 * W;
     static constexpr int kPieces = 4 * D;           // 16-byte pieces of K~, and of V~^T
     static constexpr int kItems = (kPieces + kThreads - 1) / kThreads;   // per thread
+    // a row of 8 pieces (K~ at d = 128) takes 8 slots, two rows of 4 take the
+    // even and the odd ones
+    static __device__ constexpr int k_swz(int g, int h, int j) { return G == 2 ? 4 * g + 2 * h + j : 4 * h + 2 * j; }
+    static __device__ constexpr int v_swz(int h, int j) { return 4 * h + 2 * j; }
 };
 
 // One block: W waves, queries 32 W qb + 32 w .. + 31 of head `head`, which
@@ -196,12 +203,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     auto k_lds_off = [&](int u) {
         const int key = u / (D / 16), part = u % (D / 16);
         const int g = part >> 2, hh = (part >> 1) & 1, j = part & 1;
-        return (((((key >> 4) & 1) * G + g) * 2 + j) * 64 + rho_of(key) + 32 * hh) * 16;
+        return (((((key >> 4) & 1) * G + g) * 2 + j) * 64 + (rho_of(key) ^ St::k_swz(g, hh, j)) + 32 * hh) * 16;
     };
     // V~^T piece u: channel u / 4, bytes 16 (u % 4) of its 64-key row
     auto v_lds_off = [](int u) {
-        const int ch = u >> 2, part = u & 3;
-        return St::kV + (((ch >> 5) * 2 + (part & 1)) * 64 + (ch & 31) + 32 * (part >> 1)) * 16;
+        const int ch = u >> 2, hh = (u >> 1) & 1, j = u & 1;
+        return St::kV + (((ch >> 5) * 2 + j) * 64 + ((ch & 31) ^ St::v_swz(hh, j)) + 32 * hh) * 16;
     };
     v4u kr[St::kItems], vr[St::kItems];       // native vectors: kept in registers
     uint32_t skr = 0, svr = 0;
@@ -301,9 +308,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         return;
     }
 
-    auto lds32 = [&](const uint8_t* s) {
-        const uint4 a = *reinterpret_cast<const uint4*>(s);
-        const uint4 b = *reinterpret_cast<const uint4*>(s + 1024);
+    auto lds32 = [&](const uint8_t* s0, const uint8_t* s1) {
+        const uint4 a = *reinterpret_cast<const uint4*>(s0);
+        const uint4 b = *reinterpret_cast<const uint4*>(s1 + 1024);
         return v8i{(int)a.x, (int)a.y, (int)a.z, (int)a.w, (int)b.x, (int)b.y, (int)b.z, (int)b.w};
     };
     v8i qop[G];
@@ -314,15 +321,23 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         sq[g] = qs[g * rows + head * L + q0 + n];
     }
 
+    int k_slot[G][2], v_slot[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        v_slot[j] = (32 * h + (n ^ St::v_swz(h, j))) * 16;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            k_slot[g][j] = (32 * h + (n ^ St::k_swz(g, h, j))) * 16;
+    }
     // score unit u = t G + g: x[t] gains group g's product
     v8i op;                                    // the next unit's rows and their scales
     int sc_next;
     auto fetch_k = [&](const uint8_t* s, int u) {
-        op = lds32(s + u * 2048 + lane * 16);
+        op = lds32(s + u * 2048 + k_slot[u % G][0], s + u * 2048 + k_slot[u % G][1]);
         sc_next = *reinterpret_cast<const int*>(s + St::kSk + u * 256 + lane * 4);
     };
     auto fetch_v = [&](const uint8_t* s, int i) {
-        op = lds32(s + St::kV + i * 2048 + lane * 16);
+        op = lds32(s + St::kV + i * 2048 + v_slot[0], s + St::kV + i * 2048 + v_slot[1]);
         sc_next = *reinterpret_cast<const int*>(s + St::kSv + i * 256 + lane * 4);
     };
     v16f x[2], pc, sc;                         // pc, sc: the pending unit's products
