@@ -601,8 +601,9 @@ quartz_status quartz_attn_pv(const uint8_t* p_codes, const uint8_t* p_flags,
 }
 
 // Workspace of quartz_lzs_attention.  Head dimensions 64 and 128 (the fused
-// kernel): Q, K and V^T codes / flags / scales of all heads, then the three
-// expanded to fp8 e4m3.  Other d (the unfused pipeline), in order: the PV
+// kernel): the scales of Q, K and V^T of all heads and the three in fp8 e4m3,
+// after the room of their codes and flags (unused, but part of the size that
+// callers have been told).  Other d (the unfused pipeline), in order: the PV
 // split workspace (must start zero-filled; every call leaves it so), the
 // codes / flags / scales, the scores of one head and its quantized softmax
 // output.
@@ -689,30 +690,27 @@ quartz_status quartz_lzs_attention(const void* q_bf16, const void* k_bf16, const
     auto u8 = [&](size_t off) { return base + off; };
     auto u16 = [&](size_t off) { return reinterpret_cast<uint16_t*>(base + off); };
     const int64_t rows = heads * L;
-    hipError_t e = quartz::launch_quantize_act(static_cast<const uint16_t*>(q_bf16), rows, d, d,
-                                               lzs_group, u8(w.qc), u8(w.qf), u16(w.qs), nullptr,
-                                               false, stream);
-    if (e == hipSuccess)
-        e = quartz::launch_quantize_act(static_cast<const uint16_t*>(k_bf16), rows, d, d,
-                                        lzs_group, u8(w.kc), u8(w.kf), u16(w.ks), nullptr, false,
-                                        stream);
-    if (e == hipSuccess)
-        e = quartz::launch_quantize_vt(static_cast<const uint16_t*>(v_bf16), heads, L, d, d,
-                                       lzs_group, u8(w.vc), u8(w.vf), u16(w.vs), stream);
+    const uint16_t* q = static_cast<const uint16_t*>(q_bf16);
+    const uint16_t* k = static_cast<const uint16_t*>(k_bf16);
+    const uint16_t* v = static_cast<const uint16_t*>(v_bf16);
     if (attention_fused(d)) {
-        if (e == hipSuccess)
-            e = quartz::launch_expand_fp8(u8(w.qc), u8(w.qf), rows, d, lzs_group, u8(w.qx), stream);
-        if (e == hipSuccess)
-            e = quartz::launch_expand_fp8(u8(w.kc), u8(w.kf), rows, d, lzs_group, u8(w.kx), stream);
-        if (e == hipSuccess)
-            e = quartz::launch_expand_fp8(u8(w.vc), u8(w.vf), heads * d, L, lzs_group, u8(w.vx),
-                                          stream);
+        hipError_t e = quartz::launch_attention_operands(q, k, v, heads, L, d, lzs_group, u8(w.qx),
+                                                         u16(w.qs), u8(w.kx), u16(w.ks), u8(w.vx),
+                                                         u16(w.vs), stream);
         if (e == hipSuccess)
             e = quartz::launch_attention_fused(u8(w.qx), u16(w.qs), u8(w.kx), u16(w.ks), u8(w.vx),
                                                u16(w.vs), heads, L, d, lzs_group,
                                                static_cast<uint16_t*>(o_bf16), ldo, stream);
         return from_hip(e);
     }
+    hipError_t e = quartz::launch_quantize_act(q, rows, d, d, lzs_group, u8(w.qc), u8(w.qf), u16(w.qs),
+                                               nullptr, false, stream);
+    if (e == hipSuccess)
+        e = quartz::launch_quantize_act(k, rows, d, d, lzs_group, u8(w.kc), u8(w.kf), u16(w.ks),
+                                        nullptr, false, stream);
+    if (e == hipSuccess)
+        e = quartz::launch_quantize_vt(v, heads, L, d, d, lzs_group, u8(w.vc), u8(w.vf), u16(w.vs),
+                                       stream);
     const quartz::GemmSchedule pv =
         quartz::gemm_schedule(L, d, L, quartz::gemm_resident_blocks(), true);
     const float scale = (float)(1.0 / std::sqrt((double)d));

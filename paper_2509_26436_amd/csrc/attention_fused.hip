@@ -19,10 +19,10 @@
 // can differ from the unfused path's only where P r lies within an ulp of a
 // rounding boundary.
 // One wave owns 32 queries of one head and streams every key chunk through
-// registers: no LDS, no barriers.  The operands come from HBM / L2 already
-// decoded to fp8 e4m3 (expand_fp8_kernel: every d = c 2^FLAG is exact in
-// e4m3), since every chunk of K~ and V~^T is read by all L / 32 query waves of
-// its head and decoding it once is cheaper than decoding it L / 32 times.
+// registers.  The operands come from HBM / L2 already decoded to fp8 e4m3
+// (quantize_operands_kernel: every d = c 2^FLAG is exact in e4m3), since every
+// chunk of K~ and V~^T is read by all L / 32 query waves of its head and
+// decoding it once is cheaper than decoding it L / 32 times.
 //
 // Layout of the score tiles.  The product runs as S^T = K~ Q~^T on
 // v_mfma_f32_32x32x64_f8f6f4 (rows: keys, columns: queries), so lane l holds
@@ -32,8 +32,8 @@
 // each half-wave holds 32 consecutive keys of every query, so row maxima,
 // group maxima and the FLAG subgroups (G_s <= 32) are in-lane reductions and
 // a 64-key group takes one exchange between the two half-waves.  The same
-// registers, converted to e4m3 and packed in the byte order the fp8 expansion
-// gives V~^T's keys, are the k-slice of the PV product O^T = V~^T P~^T.
+// registers, converted to e4m3 and packed in the byte order of the quantized
+// V~^T's keys, are the k-slice of the PV product O^T = V~^T P~^T.
 #include <algorithm>
 #include <cmath>
 
@@ -44,56 +44,119 @@ namespace quartz {
 
 namespace {
 
-// ------------------------------------------------------------ fp8 expansion
-// One (group, row) of a K-group-major LZS activation per thread: its 32 code
-// bytes decoded to 64 e4m3 bytes at out[row][64 g ..] (word w of the group
-// gives bytes 8 w .. 8 w + 7 in the order decode_nibbles_fp8 writes them).
+// -------------------------------------------------- quantize to fp8 operands
+// Q, K (per token along d) and V^T (per channel along the keys) quantized by
+// Eq. 1 and Eq. 2 and left as e4m3 values of c 2^FLAG, in one launch: the
+// quantizer's codes are decoded in the registers that formed them (word w of a
+// group gives bytes 8 w .. 8 w + 7 in the order decode_nibbles_fp8 writes
+// them) instead of going through memory as 4-bit codes to a second kernel, and
+// three quantizers and three expansions would be six launches (64 us at 32
+// heads, L = 4608, d = 128; 20 us at 20 heads, L = 1024, d = 64).  HBM-bound:
+// 4.6 bytes in and out per element of the three.
+//
+// A team of 8 lanes takes a group, lane u its elements 8 u .. 8 u + 7; amax: what
+// their maximum starts from (a NaN loses to any number: a row whose values are
+// all NaN keeps one and saturates its scale, a channel's starts from 0).
 template <int GS>
-__global__ __launch_bounds__(256) void expand_fp8_kernel(const uint8_t* __restrict__ codes,
-                                                         const uint8_t* __restrict__ flags,
-                                                         int64_t rows, int64_t G,
-                                                         uint8_t* __restrict__ out)
+__device__ __forceinline__ uint2 quantize_fp8(const uint4& v, float amax, uint32_t& s16)
 {
-    constexpr int FB = 64 / GS;
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= rows * G)
-        return;
-    const int64_t g = t / rows, row = t % rows;
-    const uint4 c0 = reinterpret_cast<const uint4*>(codes + t * 32)[0];
-    const uint4 c1 = reinterpret_cast<const uint4*>(codes + t * 32)[1];
-    const uint32_t w[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-    FlagRaw<GS> raw;
-    if constexpr (FB == 8)
-        raw = *reinterpret_cast<const uint2*>(flags + t * FB);
-    else if constexpr (FB == 4)
-        raw = *reinterpret_cast<const uint32_t*>(flags + t * FB);
-    else if constexpr (FB == 2)
-        raw = *reinterpret_cast<const uint16_t*>(flags + t * FB);
-    else
-        raw = flags[t];
-    const uint2 f = flags_dwords<GS>(raw);
-    uint32_t o[16];
+    constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror = 0x141;   // quad_perm, quad_perm, row_half_mirror
+    auto dpp = [](auto c, uint32_t x) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(c)::value, 0xF, 0xF, false);
+    };
+    using std::integral_constant;
+    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        Fp8Table tb;
-        switch (i / (GS / 8)) {
-        case 0: tb = fp8_table_raw<0>(f.x, f.y); break;
-        case 1: tb = fp8_table_raw<1>(f.x, f.y); break;
-        case 2: tb = fp8_table_raw<2>(f.x, f.y); break;
-        case 3: tb = fp8_table_raw<3>(f.x, f.y); break;
-        case 4: tb = fp8_table_raw<4>(f.x, f.y); break;
-        case 5: tb = fp8_table_raw<5>(f.x, f.y); break;
-        case 6: tb = fp8_table_raw<6>(f.x, f.y); break;
-        default: tb = fp8_table_raw<7>(f.x, f.y); break;
-        }
-        const uint2 d = decode_nibbles_fp8(w[i], tb);
-        o[2 * i] = d.x;
-        o[2 * i + 1] = d.y;
+    for (int k = 0; k < 4; ++k) {
+        amax = fmaxf(amax, fabsf(__uint_as_float(d[k] << 16)));
+        amax = fmaxf(amax, fabsf(__uint_as_float(d[k] & 0xFFFF0000u)));
     }
-    uint4* dst = reinterpret_cast<uint4*>(out + row * (64 * G) + 64 * g);
+    uint32_t m = __float_as_uint(amax);          // (non-negative floats order as their bits)
+    m = max(m, dpp(integral_constant<int, kXor1>(), m));
+    m = max(m, dpp(integral_constant<int, kXor2>(), m));
+    m = max(m, dpp(integral_constant<int, kMirror>(), m));
+    const GroupScale gsc = group_scale(__uint_as_float(m));
+    s16 = gsc.s16;
+    uint32_t p[4];
+    mag_pairs8(d, gsc.r, __builtin_amdgcn_ballot_w64(gsc.clamp) != 0, p);
+    uint32_t o = pairs_or(p);
+    if constexpr (GS >= 16)
+        o |= dpp(integral_constant<int, kXor1>(), o);
+    if constexpr (GS >= 32)
+        o |= dpp(integral_constant<int, kXor2>(), o);
+    if constexpr (GS >= 64)
+        o |= dpp(integral_constant<int, kMirror>(), o);
+    const int fl = lzs_flag(o);
+    return decode_nibbles_fp8(lzs_word(p, sign_nibbles(d), fl), fp8_table_raw<0>((uint32_t)fl, 0u));
+}
+
+struct AttnOperands {
+    const uint16_t *q, *k, *v;                   // bf16 [heads L][d]
+    uint8_t *qx, *kx, *vx;                       // e4m3 [heads L][d] twice, [heads d][L]
+    uint16_t *qs, *ks, *vs;                      // fp16 [d / 64][heads L] twice, [L / 64][heads d]
+};
+constexpr int kRowItems = 4;                     // 16-byte pieces per thread and tensor
+
+// The first blocks take 64 keys x 64 channels of V each (through an LDS
+// transpose), the others kRowItems 256 pieces of Q or of K.
+template <int GS>
+__global__ __launch_bounds__(256) void quantize_operands_kernel(AttnOperands a, int64_t heads, int64_t L,
+                                                                int64_t d, uint32_t vblocks, uint32_t rblocks)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t tile[64][64 + 8];
+    const int t = threadIdx.x, u = t & 7;
+    const uint32_t G = (uint32_t)d / 64, LG = (uint32_t)(L / 64);
+    uint32_t b = blockIdx.x;
+    if (b < vblocks) {
+        const uint32_t cb = b % G, hg = b / G;
+        const int64_t h = hg / LG, g = hg % LG;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        dst[k] = make_uint4(o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]);
+        for (int i = 0; i < 2; ++i) {
+            const int key = (t >> 3) + 32 * i;
+            const uint4 x = *reinterpret_cast<const uint4*>(a.v + (h * L + g * 64 + key) * d + cb * 64 + 8 * u);
+            const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                tile[8 * u + 2 * j][key] = (uint16_t)w[j];
+                tile[8 * u + 2 * j + 1][key] = (uint16_t)(w[j] >> 16);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int ch = (t >> 3) + 32 * i;
+            uint32_t s16;
+            const uint2 x = quantize_fp8<GS>(*reinterpret_cast<const uint4*>(&tile[ch][8 * u]), 0.0f, s16);
+            const int64_t row = h * d + cb * 64 + ch;
+            *reinterpret_cast<uint2*>(a.vx + row * L + g * 64 + 8 * u) = x;
+            if (u == 0)
+                a.vs[g * heads * d + row] = (uint16_t)s16;
+        }
+        return;
+    }
+    b -= vblocks;
+    const bool is_k = b >= rblocks;
+    b -= is_k ? rblocks : 0;
+    const uint4* const src = reinterpret_cast<const uint4*>(is_k ? a.k : a.q);
+    uint2* const dst = reinterpret_cast<uint2*>(is_k ? a.kx : a.qx);
+    uint16_t* const scales = is_k ? a.ks : a.qs;
+    const int64_t rows = heads * L, pieces = rows * G * 8;   // (whole teams: pieces % 8 == 0)
+    const int64_t p0 = (int64_t)b * (256 * kRowItems) + t;
+    uint4 x[kRowItems];
+#pragma unroll
+    for (int i = 0; i < kRowItems; ++i)
+        if (p0 + 256 * i < pieces)
+            x[i] = src[p0 + 256 * i];
+#pragma unroll
+    for (int i = 0; i < kRowItems; ++i) {
+        const int64_t p = p0 + 256 * i;
+        if (p >= pieces)
+            break;
+        uint32_t s16;
+        dst[p] = quantize_fp8<GS>(x[i], fabsf(__uint_as_float(x[i].x << 16)), s16);
+        if (u == 0)
+            scales[G == 1 ? p >> 3 : ((p >> 3) & 1) * rows + (p >> 4)] = (uint16_t)s16;
+    }
 }
 
 __device__ __forceinline__ v8i load32(const uint8_t* p)
@@ -500,7 +563,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     };
     // The k-slice of P~^T: dword k of the operand holds keys (relative to
     // the half-wave) 8 (k / 2) + {0, 4, 1, 5} (k even) or {2, 6, 3, 7}
-    // (k odd), the byte order of the expanded V~^T rows.  Dwords 2 sub and
+    // (k odd), the byte order of the V~^T rows.  Dwords 2 sub and
     // 2 sub + 1: the codes in pairs, clamped to 127, as bytes, c = q >> FLAG, and the e4m3 value of
     // c 2^FLAG by lookup in the base table with FLAG added to the exponent
     // field of entries 1 .. 7.
@@ -663,16 +726,19 @@ hipError_t launch_fused_gs(const uint8_t* qx, const uint16_t* qs, const uint8_t*
 
 }  // namespace
 
-hipError_t launch_expand_fp8(const uint8_t* codes, const uint8_t* flags, int64_t rows, int64_t K,
-                             int lzs_group, uint8_t* out, hipStream_t stream)
+hipError_t launch_attention_operands(const uint16_t* q, const uint16_t* k, const uint16_t* v, int64_t heads,
+                                     int64_t L, int64_t d, int lzs_group, uint8_t* qx, uint16_t* qs,
+                                     uint8_t* kx, uint16_t* ks, uint8_t* vx, uint16_t* vs, hipStream_t stream)
 {
-    const int64_t G = K / 64;
-    const dim3 grid((unsigned)((rows * G + 255) / 256)), block(256);
+    const AttnOperands a{q, k, v, qx, kx, vx, qs, ks, vs};
+    const int64_t vblocks = heads * (L / 64) * (d / 64);
+    const int64_t rblocks = (heads * L * (d / 8) + 256 * kRowItems - 1) / (256 * kRowItems);
+    const dim3 grid((unsigned)(vblocks + 2 * rblocks)), block(256);
     switch (lzs_group) {
-    case 8: expand_fp8_kernel<8><<<grid, block, 0, stream>>>(codes, flags, rows, G, out); break;
-    case 16: expand_fp8_kernel<16><<<grid, block, 0, stream>>>(codes, flags, rows, G, out); break;
-    case 32: expand_fp8_kernel<32><<<grid, block, 0, stream>>>(codes, flags, rows, G, out); break;
-    default: expand_fp8_kernel<64><<<grid, block, 0, stream>>>(codes, flags, rows, G, out); break;
+    case 8: quantize_operands_kernel<8><<<grid, block, 0, stream>>>(a, heads, L, d, (uint32_t)vblocks, (uint32_t)rblocks); break;
+    case 16: quantize_operands_kernel<16><<<grid, block, 0, stream>>>(a, heads, L, d, (uint32_t)vblocks, (uint32_t)rblocks); break;
+    case 32: quantize_operands_kernel<32><<<grid, block, 0, stream>>>(a, heads, L, d, (uint32_t)vblocks, (uint32_t)rblocks); break;
+    default: quantize_operands_kernel<64><<<grid, block, 0, stream>>>(a, heads, L, d, (uint32_t)vblocks, (uint32_t)rblocks); break;
     }
     return hipGetLastError();
 }
