@@ -44,6 +44,8 @@ namespace quartz {
 
 namespace {
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+
 // -------------------------------------------------- quantize to fp8 operands
 // Q, K (per token along d) and V^T (per channel along the keys) quantized by
 // Eq. 1 and Eq. 2 and left as e4m3 values of c 2^FLAG, in one launch: the
@@ -202,26 +204,31 @@ __device__ __forceinline__ float2 both_halves(float v)
 //   key met in the same banks: 24 % of the kernel's cycles at L = 4608);
 //   the key scales [t][g][lane] and the channel scales [i][lane]: words of an
 //   fp16 value in lanes 0 .. 31, zeros in the others.
-template <int G, int W>
+template <int G, int WQ, int S>
 struct AttnStage {
     static constexpr int D = 64 * G;
     static constexpr int kV = 64 * D;               // offsets: V~^T,
     static constexpr int kSk = kV + D * 64;         // key scales,
     static constexpr int kSv = kSk + 2 * G * 256;   // channel scales
     static constexpr int kBytes = kSv + D * 8;
-    static constexpr int kThreads = 64 * W;
+    static constexpr int kThreads = 64 * WQ * S;
     static constexpr int kPieces = 4 * D;           // 16-byte pieces of K~, and of V~^T
-    static constexpr int kItems = (kPieces + kThreads - 1) / kThreads;   // per thread
+    static constexpr int kItems = S * kPieces / kThreads;   // per thread, of S chunks
+    static_assert(S * kPieces % kThreads == 0 && (kPieces % kThreads == 0 || kThreads % kPieces == 0),
+                  "every thread moves as many, and each lies in one chunk");
     // a row of 8 pieces (K~ at d = 128) takes 8 slots, two rows of 4 take the
     // even and the odd ones
     static __device__ constexpr int k_swz(int g, int h, int j) { return G == 2 ? 4 * g + 2 * h + j : 4 * h + 2 * j; }
     static __device__ constexpr int v_swz(int h, int j) { return 4 * h + 2 * j; }
 };
 
-// One block: W waves, queries 32 W qb + 32 w .. + 31 of head `head`, which
-// share the staged chunks.  qx / kx: [heads L][64 G] e4m3, qs / ks:
-// [G][heads L] fp16; vx: [heads d][L] e4m3 (V^T), vs: [L / 64][heads d] fp16;
-// o: bf16 [L][ldo], head h at columns h d ...
+// One block: WQ S waves, queries 32 WQ qb .. of head `head`: S teams of WQ
+// waves of 32 queries each, which take the chunks in turn (team k chunks k,
+// k + S, ..) and share the staged ones; the teams' sums meet after pass 1 and
+// their outputs at the end, in LDS.  Block b of the launch is block first + b
+// of heads qblocks.  qx / kx: [heads L][64 G] e4m3, qs / ks: [G][heads L]
+// fp16; vx: [heads d][L] e4m3 (V^T), vs: [L / 64][heads d] fp16; o: bf16
+// [L][ldo], head h at columns h d ...
 //
 // What bounds it is the issue of vector instructions (per 64-key chunk and
 // wave 24 MFMAs at d = 128 beside ~520, 64 of them exponentials), so both
@@ -231,36 +238,41 @@ struct AttnStage {
 // beside a piece of the softmax or of the quantizer; the operands are read
 // from LDS a slot ahead.  Pass 2 runs the PV units of the chunk before, then
 // the score units of the chunk after the one it quantizes.
-template <int GS, int G, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void lzs_attention_fused_kernel(
+template <int GS, int G, int WQ, int S>
+__global__ __launch_bounds__(64 * WQ * S) __attribute__((amdgpu_waves_per_eu(2, 2))) void lzs_attention_fused_kernel(
     const uint8_t* __restrict__ qx, const uint16_t* __restrict__ qs,
     const uint8_t* __restrict__ kx, const uint16_t* __restrict__ ks,
     const uint8_t* __restrict__ vx, const uint16_t* __restrict__ vs, int64_t heads, int64_t L,
-    float kexp, uint16_t* __restrict__ o, int64_t ldo, int64_t qblocks)
+    float kexp, uint16_t* __restrict__ o, int64_t ldo, uint32_t first_block, uint32_t qblocks)
 {
-    using St = AttnStage<G, W>;
+    using St = AttnStage<G, WQ, S>;
     constexpr int D = St::D;
     constexpr int TV = D / 32;                 // channel tiles of the PV product
     constexpr int NU = 2 * G;                  // score units of a chunk
-    __shared__ __attribute__((aligned(16))) uint8_t smem[2][St::kBytes];
+    __shared__ __attribute__((aligned(16))) uint8_t smem[2][S][St::kBytes];
 
     // blocks of one head on one XCD (consecutive block ids go round robin
     // over the 8 XCDs), so its K~ / V~^T chunks are shared in that L2
-    const int64_t total = heads * qblocks;
-    const int64_t bid = blockIdx.x;
-    const int64_t logical = total % 8 == 0 ? (bid % 8) * (total / 8) + bid / 8 : bid;
+    const uint32_t total = gridDim.x, bid = blockIdx.x;
+    const uint32_t logical = first_block + (total % 8 == 0 ? (bid % 8) * (total / 8) + bid / 8 : bid);
     const int64_t head = logical / qblocks;
     const int tid = threadIdx.x;
-    const int64_t q0 = (logical % qblocks) * (32 * W) + __builtin_amdgcn_readfirstlane(tid >> 6) * 32;
-    // a wave past the end of a ragged last block still loads and waits at
-    // the barriers, and computes nothing (wave-uniform)
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int team = wave / WQ, wq = wave % WQ;
+    const int64_t qb = (int64_t)(logical % qblocks) * (32 * WQ);
+    if (qb >= L)
+        return;                                // a ragged head's last blocks
+    const int64_t q0 = qb + wq * 32;
+    // a wave past the end of a ragged block still loads and waits at the
+    // barriers, and computes nothing (wave-uniform)
     const bool active = q0 < L;
     const int lane = tid & 63;
     const int n = lane & 31, h = lane >> 5;
     const int64_t rows = heads * L;
-    const int chunks = (int)(L / 64);
+    const int chunks = (int)(L / 64), steps = (chunks + S - 1) / S;
 
-    // ---- cooperative staging: thread tid moves pieces tid + 64 W p
+    // ---- cooperative staging of a step's S chunks: thread tid moves pieces
+    // tid + 64 WQ S p, in two halves (K~, V~^T) through the same registers
     // K~ piece u: key u / (D / 16), bytes 16 (u % (D / 16)) of its row
     auto rho_of = [](int key) { return 8 * ((key >> 2) & 3) + 4 * (key >> 5) + (key & 3); };
     auto k_lds_off = [&](int u) {
@@ -273,99 +285,112 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         const int ch = u >> 2, hh = (u >> 1) & 1, j = u & 1;
         return St::kV + (((ch >> 5) * 2 + j) * 64 + ((ch & 31) ^ St::v_swz(hh, j)) + 32 * hh) * 16;
     };
-    v4u kr[St::kItems], vr[St::kItems];       // native vectors: kept in registers
-    uint32_t skr = 0, svr = 0;
-    auto load_k = [&](int c) {
-        c = min(c, chunks - 1);
-        const uint8_t* kc = kx + (head * L + 64 * c) * D;
-#pragma unroll
-        for (int p = 0; p < St::kItems; ++p)
-            if (tid + St::kThreads * p < St::kPieces)
-                kr[p] = reinterpret_cast<const v4u*>(kc)[tid + St::kThreads * p];
-        if (tid < 64 * G)
-            skr = ks[(tid >> 6) * rows + head * L + 64 * c + (tid & 63)];
-    };
-    auto load_v = [&](int c) {
-        c = min(c, chunks - 1);
+    v4u pieces[St::kItems];                    // native vectors: kept in registers
+    uint32_t scale = 0;
+    auto chunk_of = [&](int step, int k) { return min(step * S + k, chunks - 1); };
+    constexpr int T = St::kThreads, kP = St::kPieces;
+    auto chunk_of_piece = [&](int p) { return T <= kP ? T * p / kP : T / kP * p + tid / kP; };
+    // a step's scales: thread tid the chunk, group or channel tid names
+    const int ks_k = tid / (64 * G), ks_i = tid % (64 * G), vs_k = tid / D, vs_i = tid % D;
+    static_assert(T >= S * D, "a thread per scale");
+    auto load_k = [&](int step) {
 #pragma unroll
         for (int p = 0; p < St::kItems; ++p) {
-            const int u = tid + St::kThreads * p;
-            if (u < St::kPieces)
-                vr[p] = *reinterpret_cast<const v4u*>(vx + (head * D + (u >> 2)) * L + 64 * c + 16 * (u & 3));
+            const int k = chunk_of_piece(p), u = (tid + T * p) % kP;
+            pieces[p] = reinterpret_cast<const v4u*>(kx + (head * L + 64 * chunk_of(step, k)) * D)[u];
         }
-        if (tid < D)
-            svr = vs[c * heads * D + head * D + tid];
+        if (T == S * D || ks_k < S)
+            scale = ks[(ks_i >> 6) * rows + head * L + 64 * chunk_of(step, ks_k) + (ks_i & 63)];
+    };
+    auto load_v = [&](int step) {
+#pragma unroll
+        for (int p = 0; p < St::kItems; ++p) {
+            const int k = chunk_of_piece(p), u = (tid + T * p) % kP;
+            pieces[p] = *reinterpret_cast<const v4u*>(vx + (head * D + (u >> 2)) * L + 64 * chunk_of(step, k) +
+                                                          16 * (u & 3));
+        }
+        if (T == S * D || vs_k < S)
+            scale = vs[chunk_of(step, vs_k) * heads * D + head * D + vs_i];
     };
     auto store_k = [&](int b) {
-        uint8_t* s = smem[b];
 #pragma unroll
-        for (int p = 0; p < St::kItems; ++p)
-            if (tid + St::kThreads * p < St::kPieces)
-                *reinterpret_cast<v4u*>(s + k_lds_off(tid + St::kThreads * p)) = kr[p];
-        if (tid < 64 * G) {
-            const int key = tid & 63;
-            *reinterpret_cast<uint32_t*>(s + St::kSk + ((((key >> 4) & 1) * G + (tid >> 6)) * 64 + rho_of(key)) * 4) = skr;
+        for (int p = 0; p < St::kItems; ++p) {
+            const int k = chunk_of_piece(p), u = (tid + T * p) % kP;
+            *reinterpret_cast<v4u*>(smem[b][k] + k_lds_off(u)) = pieces[p];
+        }
+        if (T == S * D || ks_k < S) {
+            const int key = ks_i & 63;
+            *reinterpret_cast<uint32_t*>(smem[b][ks_k] + St::kSk +
+                                         ((((key >> 4) & 1) * G + (ks_i >> 6)) * 64 + rho_of(key)) * 4) = scale;
         }
     };
     auto store_v = [&](int b) {
-        uint8_t* s = smem[b];
 #pragma unroll
-        for (int p = 0; p < St::kItems; ++p)
-            if (tid + St::kThreads * p < St::kPieces)
-                *reinterpret_cast<v4u*>(s + v_lds_off(tid + St::kThreads * p)) = vr[p];
-        if (tid < D)
-            *reinterpret_cast<uint32_t*>(s + St::kSv + ((tid >> 5) * 64 + (tid & 31)) * 4) = svr;
+        for (int p = 0; p < St::kItems; ++p) {
+            const int k = chunk_of_piece(p), u = (tid + T * p) % kP;
+            *reinterpret_cast<v4u*>(smem[b][k] + v_lds_off(u)) = pieces[p];
+        }
+        if (T == S * D || vs_k < S)
+            *reinterpret_cast<uint32_t*>(smem[b][vs_k] + St::kSv + ((vs_i >> 5) * 64 + (vs_i & 31)) * 4) = scale;
     };
     // (loads in flight stay in flight)
     auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
-    // ---- what the waves share, in order: pass 1 reads chunk c from buffer
-    // c & 1 while c + 2 waits in registers to replace it; pass 2 at chunk c
-    // writes K~ of c + 2 and V~^T of c into buffer c & 1 and reads K~ of c + 1
-    // and V~^T of c - 1 from the other.
-    for (int i = tid; i < 2 * (2 * G + TV) * 32; i += St::kThreads) {   // the zeros of the scales' upper lanes
-        const int b = i / ((2 * G + TV) * 32), row = i / 32 % (2 * G + TV);
-        *reinterpret_cast<uint32_t*>(smem[b] + St::kSk + row * 256 + 128 + (i & 31) * 4) = 0;
+    // ---- what the waves share, in order: pass 1 reads step c from buffer
+    // c & 1, which step c + 2 then replaces; pass 2 at step c writes K~ of c + 2
+    // and V~^T of c into buffer c & 1 and reads K~ of c + 1 and V~^T of c - 1
+    // from the other.
+    for (int i = tid; i < 2 * S * (2 * G + TV) * 32; i += T) {   // the zeros of the scales' upper lanes
+        const int row = i / 32 % (2 * G + TV), b = i / 32 / (2 * G + TV);
+        *reinterpret_cast<uint32_t*>(smem[b / S][b % S] + St::kSk + row * 256 + 128 + (i & 31) * 4) = 0;
     }
     auto begin1 = [&] {
         load_k(0);
         store_k(0);
         load_k(1);
         store_k(1);
-        load_k(2);
         barrier();
-    };
-    auto refill1 = [&](int c) {                // chunk c has been read
-        store_k(c & 1);
-        load_k(c + 3);
     };
     auto begin2 = [&] {
         barrier();
         load_k(0);
         store_k(0);
         load_k(1);
-        load_v(0);
         store_k(1);
-        store_v(1);                            // (stands in for chunk -1, whose codes are 0)
-        load_k(2);
+        load_v(0);
+        store_v(1);                            // (stands in for step -1, whose codes are 0)
         barrier();
     };
-    auto refill2 = [&](int c) {
-        store_k(c & 1);
-        store_v(c & 1);
-        load_k(c + 3);
-        load_v(c + 1);
+    // the sums of a team's queries: [team][wq][n] of (nf, l), in the first buffer
+    float2* const sums = reinterpret_cast<float2*>(smem[0][0]);
+    // a team's partial outputs: row tile i of wave wq, for the team i % S that stores it
+    auto partial = [&](int i, int from) {
+        const int owner = i % S, rank = from < owner ? from : from - 1;
+        return reinterpret_cast<v4f*>(smem[0][0] + ((i * (S - 1) + rank) * WQ + wq) * 4096 + lane * 16);
     };
+    static_assert(S == 1 || TV * (S - 1) * WQ * 4096 <= (int)sizeof(smem), "partial outputs fit");
     if (!active) {
         begin1();
-        for (int c = 0; c < chunks; ++c) {
+        for (int c = 0; c < steps; ++c) {
+            load_k(c + 2);
             barrier();
-            refill1(c);
+            store_k(c & 1);
+        }
+        if constexpr (S > 1) {
+            barrier();
+            barrier();
         }
         begin2();
         barrier();
-        for (int c = 0; c < chunks; ++c) {
-            refill2(c);
+        for (int c = 0; c < steps; ++c) {
+            load_k(c + 2);
+            store_k(c & 1);
+            load_v(c);
+            store_v(c & 1);
+            barrier();
+        }
+        if constexpr (S > 1) {
+            barrier();
             barrier();
         }
         return;
@@ -420,7 +445,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // is formed otherwise.
     constexpr float kMost = 4096.0f;
     float nf = 1e30f, l = 0.0f;                // (the first tile's sum is infinite)
-    auto tile_sum = [&](auto tc) {
+    auto tile_sum = [&](auto tc, bool exists) {
         const v16f& v = x[decltype(tc)::value];
         // four independent chains
         auto sum = [&] {
@@ -433,7 +458,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             return (s4[0] + s4[1]) + (s4[2] + s4[3]);
         };
         float s = sum();
-        if (__builtin_amdgcn_ballot_w64(s > kMost)) {
+        if (__builtin_amdgcn_ballot_w64(s > kMost) && exists) {
             float m = v[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r)
@@ -443,16 +468,18 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             nf = to;
             s = sum();
         }
-        l += s;
+        l += exists ? s : 0.0f;
     };
     begin1();
-    fetch_k(smem[0], 0);
+    fetch_k(smem[0][team], 0);
     pc = mfma_fp8(op, qop[0]);
     sc = mfma_outer(sc_next, sq[0]);
-    fetch_k(smem[0], 1);
-    for (int c = 0; c < chunks; ++c) {
-        const uint8_t* const here = smem[c & 1];
-        const uint8_t* const next = smem[(c & 1) ^ 1];
+    fetch_k(smem[0][team], 1);
+    for (int c = 0; c < steps; ++c) {
+        const uint8_t* const here = smem[c & 1][team];
+        const uint8_t* const next = smem[(c & 1) ^ 1][team];
+        const bool exists = S == 1 || c * S + team < chunks;
+        load_k(c + 2);
         auto slot = [&](auto uc) {
             constexpr int u = decltype(uc)::value;
             if constexpr (u == NU - 2)
@@ -471,7 +498,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             pc = pn;
             fence();
             if constexpr (u % G == G - 1)
-                tile_sum(std::integral_constant<int, u / G>());
+                tile_sum(std::integral_constant<int, u / G>(), exists);
             fence();
         };
         slot(std::integral_constant<int, 0>());
@@ -480,13 +507,28 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             slot(std::integral_constant<int, 2>());
             slot(std::integral_constant<int, 3>());
         }
-        refill1(c);
+        store_k(c & 1);
     }
     {
         // the two half-waves' keys of the same query (identical result in both)
         const float2 n2 = both_halves(nf), l2 = both_halves(l);
         nf = fminf(n2.x, n2.y);
         l = l2.x * __builtin_amdgcn_exp2f(nf - n2.x) + l2.y * __builtin_amdgcn_exp2f(nf - n2.y);
+    }
+    if constexpr (S > 1) {                     // the teams', in their order (identical result in all)
+        barrier();
+        sums[(team * WQ + wq) * 32 + n] = {nf, l};
+        barrier();
+        float2 t[S];
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            t[k] = sums[(k * WQ + wq) * 32 + n];
+            nf = fminf(nf, t[k].x);
+        }
+        l = 0.0f;
+#pragma unroll
+        for (int k = 0; k < S; ++k)
+            l += t[k].y * __builtin_amdgcn_exp2f(nf - t[k].x);
     }
     const float inv_l = 1.0f / l;
 
@@ -496,9 +538,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     for (int i = 0; i < TV; ++i)
         acc[i] = v16f{};
     begin2();
-    auto first = [&](auto uc) {                // the scores of chunk 0, the last unit left pending
+    auto first = [&](auto uc) {                // the scores of step 0, the last unit left pending
         constexpr int u = decltype(uc)::value;
-        fetch_k(smem[0], u);
+        fetch_k(smem[0][team], u);
         pc = mfma_fp8(op, qop[u % G]);
         sc = mfma_outer(sc_next, sq[u % G]);
         if constexpr (u + 1 < NU)
@@ -511,7 +553,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         first(std::integral_constant<int, 3>());
     }
     barrier();
-    fetch_v(smem[1], 0);
+    fetch_v(smem[1][team], 0);
 
     // the quantized probabilities of the chunk before (operand, group scale)
     v8i pop = {};
@@ -534,7 +576,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         return __float_as_uint(fmaf(__builtin_amdgcn_exp2f(fmaf(v, kexp, nf)), R, kMagic));
     };
     float m8[4];
-    auto group_scale_of = [&] {
+    auto group_scale_of = [&](bool exists) {
         float xm = fmaxf(fmaxf(m8[0], m8[1]), fmaxf(m8[2], m8[3]));
         const float2 x2 = both_halves(xm);
         xm = fmaxf(x2.x, x2.y);
@@ -543,7 +585,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         const float alpha = __builtin_amdgcn_exp2f(fmaf(xm, kexp, nf)) * inv_l;
         const float a0 = alpha * kInv127;
         const _Float16 s16 = (_Float16)fmaf(fmaf(-127.0f, a0, alpha), kInv127, a0);
-        const uint32_t sbits = __builtin_bit_cast(uint16_t, s16);
+        const uint32_t sbits = exists ? __builtin_bit_cast(uint16_t, s16) : 0u;
         const float s = (float)s16, r0 = __builtin_amdgcn_rcpf(s);
         R = sbits == 0 ? 0.0f : inv_l * fmaf(r0, fmaf(-s, r0, 1.0f), r0);
         spnew = (int)sbits;
@@ -594,14 +636,21 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             acc[i][r] = fmaf(pc[r], sc[r], acc[i][r]);
         asm volatile("" : "+v"(acc[i]));
     };
-    for (int c = 0; c < chunks; ++c) {
-        const uint8_t* const there = smem[(c & 1) ^ 1];
-        refill2(c);
+    for (int c = 0; c < steps; ++c) {
+        const uint8_t* const there = smem[(c & 1) ^ 1][team];
+        const bool exists = S == 1 || c * S + team < chunks;
+        load_k(c + 2);
         auto slot = [&](auto kc) {
-            // units: TV of PV (chunk c - 1), NU scores (chunk c + 1)
+            // units: TV of PV (step c - 1), NU scores (step c + 1)
             constexpr int k = decltype(kc)::value;
-            if constexpr (k == TV + NU - 1)
+            if constexpr (k == (TV + NU) / 2) {
+                store_k(c & 1);
+                load_v(c);
+            }
+            if constexpr (k == TV + NU - 1) {
+                store_v(c & 1);
                 barrier();                     // all of `there` is read, the other buffer is there
+            }
             v16f pn;
             if constexpr (k < TV)
                 pn = mfma_fp8(op, pop);
@@ -614,7 +663,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             else if constexpr (k + 1 < TV + NU)
                 fetch_k(there, k + 1 - TV);
             else
-                fetch_v(smem[c & 1], 0);
+                fetch_v(smem[c & 1][team], 0);
             fence();
             if constexpr (k == 0)
                 score(std::integral_constant<int, NU - 1>(), pc, sc);
@@ -636,7 +685,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 m8[1] = max8(0, 1);
                 m8[2] = max8(1, 0);
                 m8[3] = max8(1, 1);
-                group_scale_of();
+                group_scale_of(exists);
             } else if constexpr (k <= TV) {
                 constexpr int per = 4 / TV;
 #pragma unroll
@@ -658,14 +707,41 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         pop = pnew;
         sp = spnew;
     }
-    // the PV units of the last chunk (the first one's rows are fetched)
+    // the PV units of the last step (the first one's rows are fetched)
 #pragma unroll
     for (int i = 0; i < TV; ++i) {
         if (i > 0)
-            fetch_v(smem[(chunks - 1) & 1], i);
+            fetch_v(smem[(steps - 1) & 1][team], i);
         pc = mfma_fp8(op, pop);
         sc = mfma_outer(sc_next, sp);
         add_pv(i);
+    }
+    if constexpr (S > 1) {
+        barrier();
+#pragma unroll
+        for (int i = 0; i < TV; ++i)
+            if (team != i % S)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    partial(i, team)[64 * q] = v4f{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+        barrier();
+#pragma unroll
+        for (int i = 0; i < TV; ++i)
+            if (team == i % S) {
+                v16f sum;
+#pragma unroll
+                for (int k = 0; k < S; ++k)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        v4f y = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+                        if (k != i % S)
+                            y = partial(i, k)[64 * q];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            sum[4 * q + e] = k == 0 ? y[e] : sum[4 * q + e] + y[e];
+                    }
+                acc[i] = sum;
+            }
     }
     // O^T tile i, register r: channel 32 i + 8 (r / 4) + 4 h + r % 4 of query
     // q0 + n; four consecutive channels per 8-byte store
@@ -673,7 +749,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     typedef float f2 __attribute__((ext_vector_type(2)));
     uint16_t* orow = o + (q0 + n) * ldo + head * D;
 #pragma unroll
-    for (int i = 0; i < TV; ++i)
+    for (int i = 0; i < TV; ++i) {
+        if (team != i % S)
+            continue;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const f2 a = {acc[i][4 * j], acc[i][4 * j + 1]};
@@ -682,45 +760,56 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                              __builtin_bit_cast(uint32_t, __builtin_convertvector(b, bf2))};
             *reinterpret_cast<uint2*>(orow + 32 * i + 8 * j + 4 * h) = v;
         }
+    }
 }
 
-template <int GS, int W>
+template <int GS, int WQ, int S>
 void launch_fused_w(const uint8_t* qx, const uint16_t* qs, const uint8_t* kx, const uint16_t* ks,
                     const uint8_t* vx, const uint16_t* vs, int64_t heads, int64_t L, int64_t d,
-                    uint16_t* o, int64_t ldo, hipStream_t stream)
+                    uint16_t* o, int64_t ldo, int64_t first, int64_t count, int64_t qblocks, hipStream_t stream)
 {
-    const int64_t qblocks = (L + 32 * W - 1) / (32 * W);
-    const dim3 grid((unsigned)(heads * qblocks)), block(64 * W);
+    const dim3 grid((unsigned)count), block(64 * WQ * S);
     const float kexp = (float)(1.4426950408889634 / std::sqrt((double)d));
     if (d == 64)
-        lzs_attention_fused_kernel<GS, 1, W><<<grid, block, 0, stream>>>(qx, qs, kx, ks, vx, vs, heads, L,
-                                                                          kexp, o, ldo, qblocks);
+        lzs_attention_fused_kernel<GS, 1, WQ, S><<<grid, block, 0, stream>>>(
+            qx, qs, kx, ks, vx, vs, heads, L, kexp, o, ldo, (uint32_t)first, (uint32_t)qblocks);
     else
-        lzs_attention_fused_kernel<GS, 2, W><<<grid, block, 0, stream>>>(qx, qs, kx, ks, vx, vs, heads, L,
-                                                                          kexp, o, ldo, qblocks);
+        lzs_attention_fused_kernel<GS, 2, WQ, S><<<grid, block, 0, stream>>>(
+            qx, qs, kx, ks, vx, vs, heads, L, kexp, o, ldo, (uint32_t)first, (uint32_t)qblocks);
 }
 
-// Block shape: 8 query waves per block share each staged chunk among twice
-// the queries of 4 and cost ~8.5 % less per wave, but run one block per CU,
-// so a launch takes whole rounds of 8-wave blocks; with 4-wave blocks (two
-// per CU) a partial last round is spread one block per CU and runs faster
-// per block, so the time grows about linearly with the block count.  Take 8
-// waves only when the last round of 8-wave blocks is nearly full (measured
-// at L = 4608: 40 heads, 2.81 rounds, 0.88 against 0.93 ms; 32 and 64 heads,
-// 2.25 and 4.5 rounds, favour 4 waves).
+// Two blocks of 4 waves (128 queries each) fill a compute unit, and take whole
+// rounds of the device (one block of 8 waves, whose barriers hold more waves,
+// is 2 to 9 % slower at 48 heads, L = 4096).  What is left over is split among
+// teams so that it is one shorter round: up to a quarter of one by 4 teams, up
+// to a half by 2, up to three quarters by 2 in blocks of 64 queries; more than
+// that runs on unsplit.  Measured in us, d = 128, for unsplit / 2 teams of 4
+// waves / 2 of 2 / 4 of 2 left-over blocks: 32 heads x 4608, a quarter, 564 /
+// 537 / 510 / 491; 12 x 2048, 0.38, 75 / 65 / 68 / 76; 24 x 2048, 0.75, 110 /
+// 121 / 103 / 113; 40 x 4608, 0.81, 612 in one launch / 654 / 664 / 688.  Four
+// teams want two chunks each: 8 x 256 14.3 with two, 15.0 with four.
 template <int GS>
 hipError_t launch_fused_gs(const uint8_t* qx, const uint16_t* qs, const uint8_t* kx,
                            const uint16_t* ks, const uint8_t* vx, const uint16_t* vs,
                            int64_t heads, int64_t L, int64_t d, uint16_t* o, int64_t ldo,
                            hipStream_t stream)
 {
-    const int64_t cus = std::max<int64_t>(1, device_compute_units());
-    const int64_t blocks8 = heads * ((L + 255) / 256);
-    const int64_t rounds8 = (blocks8 + cus - 1) / cus;
-    if (rounds8 * cus * 100 <= blocks8 * 109)
-        launch_fused_w<GS, 8>(qx, qs, kx, ks, vx, vs, heads, L, d, o, ldo, stream);
+    const int64_t round = 2 * std::max<int64_t>(1, device_compute_units());
+    const int64_t per_head = (L + 127) / 128, blocks = heads * per_head;
+    const int64_t over = blocks % round;
+    const int64_t rest = 4 * over > 3 * round ? 0 : over, whole = blocks - rest;
+    if (whole > 0)
+        launch_fused_w<GS, 4, 1>(qx, qs, kx, ks, vx, vs, heads, L, d, o, ldo, 0, whole, per_head, stream);
+    if (rest == 0)
+        return hipGetLastError();
+    if (4 * rest <= round && L >= 8 * 64)
+        launch_fused_w<GS, 2, 4>(qx, qs, kx, ks, vx, vs, heads, L, d, o, ldo, 2 * whole, 2 * rest, 2 * per_head,
+                                 stream);
+    else if (4 * rest > round && 2 * rest <= round)
+        launch_fused_w<GS, 4, 2>(qx, qs, kx, ks, vx, vs, heads, L, d, o, ldo, whole, rest, per_head, stream);
     else
-        launch_fused_w<GS, 4>(qx, qs, kx, ks, vx, vs, heads, L, d, o, ldo, stream);
+        launch_fused_w<GS, 2, 2>(qx, qs, kx, ks, vx, vs, heads, L, d, o, ldo, 2 * whole, 2 * rest, 2 * per_head,
+                                 stream);
     return hipGetLastError();
 }
 
