@@ -474,14 +474,47 @@ quartz_status quartz_lzs_attention(const void* q_bf16, const void* k_bf16, const
                                    size_t workspace_bytes, hipStream_t stream);
 
 /*
+ * quartz_w4a4_layer_kernel (host only, needs no GPU): the kernel that a layer
+ * call of these sizes launches on a device of `blocks` compute units.
+ *   layer     QUARTZ_LAYER_*: LINEAR is quartz_w4a4_linear, _ws and _noalloc;
+ *             a convolution has M = images * H * W and K = 9 C.
+ *   split     1: with a workspace (or quartz_w4a4_linear_noalloc), 0: without.
+ *   kernel    host int32[5]: QUARTZ_KERNEL_*, the rows and columns of its
+ *             tiles, the teams of waves that share a tile's groups (1 but for
+ *             QUARTZ_KERNEL_WIDE), and 1 if tiles are cut along K, so that
+ *             the workspace (or the scratch array) is used.
+ * The wide kernel runs whole tiles and uses no workspace.  It adds the groups
+ * of an output in ascending order when one team has the tile, as the other
+ * two do when nothing is split; teams add every 2nd or 4th group each, and
+ * their sums at the end.
+ * QUARTZ_ERR_SHAPE, QUARTZ_ERR_UNSUPPORTED: sizes and options the layer does
+ * not take; QUARTZ_ERR_NULL: no `kernel`.
+ */
+#define QUARTZ_LAYER_LINEAR 0
+#define QUARTZ_LAYER_QUANTIZE 1
+#define QUARTZ_LAYER_STATIC 2
+#define QUARTZ_LAYER_ASYM 3
+#define QUARTZ_LAYER_CONV3X3 4
+#define QUARTZ_LAYER_CONV3X3_STATIC 5
+
+#define QUARTZ_KERNEL_WIDE 0
+#define QUARTZ_KERNEL_LINEAR 1
+#define QUARTZ_KERNEL_GEMM 2
+
+quartz_status quartz_w4a4_layer_kernel(int64_t M, int64_t N, int64_t K, int32_t lzs_group,
+                                       int32_t epilogue, int32_t layer, int32_t split,
+                                       int32_t blocks, int32_t* kernel);
+
+/*
  * quartz_w4a4_linear_schedule (host only, needs no GPU): the GEMM work
  * schedule for a persistent grid of at most `blocks` workgroups (the entry
  * points use the device's compute-unit count), with (split = 1, as
  * quartz_w4a4_linear_ws) or without (split = 0, as quartz_w4a4_linear) tiles
- * cut along K, for tiles of 128 x 256 (tiles = 0: quartz_w4a4_linear and its
- * variants, quartz_w4a4_linear_quantize, quartz_w4a4_linear_static and
- * quartz_w4a4_linear_asym) or of 256 x 128 (tiles = 1: the convolutions, the
- * exact integer accumulator and the attention products).
+ * cut along K, for tiles of 128 x 256 (tiles = 0: QUARTZ_KERNEL_LINEAR) or of
+ * 256 x 128 (tiles = 1: QUARTZ_KERNEL_GEMM, the exact integer accumulator and
+ * the attention products).  A layer call follows it unless it launches
+ * QUARTZ_KERNEL_WIDE (quartz_w4a4_layer_kernel), whose tiles are never split;
+ * the workspace's size is that of the schedule in either case.
  *   schedule  host int32[10]: tiles_n, groups, split, blocks, whole tiles of
  *             workgroup 0, sk_first, sk_tiles, sk_blocks, sk_q, sk_r.
  *   segments  host int32[capacity][10], one row per (workgroup, segment):

@@ -33,7 +33,7 @@ __all__ = [
     "quartz_quantize_vt", "quartz_attn_scores", "quartz_softmax_quantize",
     "quartz_attn_pv_workspace_bytes", "quartz_attn_pv", "quartz_lzs_attention_workspace_bytes",
     "quartz_lzs_attention", "quantize_vt", "attn_scores", "softmax_quantize", "attn_pv",
-    "attention_workspace", "lzs_attention",
+    "attention_workspace", "lzs_attention", "quartz_w4a4_layer_kernel", "layer_kernel",
 ]
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -58,7 +58,7 @@ EXPORTED_SYMBOLS = (
     "quartz_w4a4_linear_noalloc", "quartz_w4a4_linear_noalloc_max_bytes",
     "quartz_quantize_vt", "quartz_attn_scores", "quartz_softmax_quantize",
     "quartz_attn_pv_workspace_bytes", "quartz_attn_pv", "quartz_lzs_attention_workspace_bytes",
-    "quartz_lzs_attention",
+    "quartz_lzs_attention", "quartz_w4a4_layer_kernel",
 )
 
 
@@ -128,6 +128,8 @@ def load() -> ctypes.CDLL:
     lib.quartz_w4a4_conv3x3_static.restype = I32
     lib.quartz_w4a4_linear_schedule.argtypes = [I64, I64, I64, I32, I32, I32, P, P, I64]
     lib.quartz_w4a4_linear_schedule.restype = I64
+    lib.quartz_w4a4_layer_kernel.argtypes = [I64, I64, I64, I32, I32, I32, I32, I32, P]
+    lib.quartz_w4a4_layer_kernel.restype = I32
     lib.quartz_unpack_weight.argtypes = [P, I64, I64, I32, P, P]
     lib.quartz_unpack_weight.restype = I32
     lib.quartz_w4a4_gemm_i32.argtypes = [P, P, P, P, I64, I64, I64, I32, I32, P]
@@ -257,6 +259,10 @@ def quartz_w4a4_conv3x3_static(codes, flags, act_scale, w_packed, bias, y, image
 def quartz_w4a4_linear_schedule(M, N, K, blocks, split, tiles, schedule, segments, capacity) -> int:
     return int(load().quartz_w4a4_linear_schedule(M, N, K, blocks, split, tiles, schedule, segments,
                                                   capacity))
+
+
+def quartz_w4a4_layer_kernel(M, N, K, lzs_group, epilogue, layer, split, blocks, kernel) -> int:
+    return load().quartz_w4a4_layer_kernel(M, N, K, lzs_group, epilogue, layer, split, blocks, kernel)
 
 
 def quartz_unpack_weight(w_packed, N, K, group_size, wq, stream) -> int:
@@ -664,6 +670,24 @@ def linear_schedule(M: int, N: int, K: int, blocks: int, split: bool = True, til
                                      seg.ctypes.data, n)
     assert n2 == n
     return dict(zip(SCHEDULE_FIELDS, (int(v) for v in sched))), seg[:n]
+
+
+LAYERS = ("linear", "quantize", "static", "asym", "conv3x3", "conv3x3_static")
+KERNELS = ("wide", "linear", "gemm")
+
+
+def layer_kernel(M: int, N: int, K: int, lzs_group: int = 16, layer: str = "linear",
+                 epilogue: int = EPI_NONE, split: bool = True, blocks: int = 256) -> dict:
+    """The kernel that a layer call launches on a device of ``blocks`` compute units
+    (quartz_w4a4_layer_kernel, host only): kernel (one of KERNELS), tile rows and columns,
+    teams per tile, and whether tiles are cut along K (the workspace is used).  ``layer``: one
+    of LAYERS; ``split``: with a workspace, or w4a4_linear_noalloc."""
+    out = (ctypes.c_int32 * 5)()
+    st = quartz_w4a4_layer_kernel(M, N, K, lzs_group, epilogue, LAYERS.index(layer), int(split),
+                                  blocks, ctypes.addressof(out))
+    _check(st, "quartz_w4a4_layer_kernel")
+    return {"kernel": KERNELS[out[0]], "rows": out[1], "cols": out[2], "teams": out[3],
+            "split": bool(out[4])}
 
 
 def unpack_weight(w: PackedWeight, stream=None):

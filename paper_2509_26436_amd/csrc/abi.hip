@@ -1,5 +1,6 @@
 // C-ABI entry points of libquartz.so: host-side validation, then the launch on
 // the caller's stream.  See include/quartz.h for the contract of each call.
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 
@@ -458,6 +459,37 @@ int64_t quartz_w4a4_linear_schedule(int64_t M, int64_t N, int64_t K, int32_t blo
             return -2;
     }
     return n;
+}
+
+quartz_status quartz_w4a4_layer_kernel(int64_t M, int64_t N, int64_t K, int32_t lzs_group,
+                                       int32_t epilogue, int32_t layer, int32_t split,
+                                       int32_t blocks, int32_t* kernel)
+{
+    if (!lzs_ok(lzs_group) || (epilogue != QUARTZ_EPI_NONE && epilogue != QUARTZ_EPI_GELU_TANH) ||
+        layer < QUARTZ_LAYER_LINEAR || layer > QUARTZ_LAYER_CONV3X3_STATIC)
+        return QUARTZ_ERR_UNSUPPORTED;
+    const bool conv = layer == QUARTZ_LAYER_CONV3X3 || layer == QUARTZ_LAYER_CONV3X3_STATIC;
+    if (M <= 0 || N <= 0 || K <= 0 || !size_ok(M, K) || !size_ok(N, K) || blocks <= 0 ||
+        (layer == QUARTZ_LAYER_QUANTIZE && N % 64 != 0) || (conv && (K % 576 != 0 || M >= kMaxConvPixels)))
+        return QUARTZ_ERR_SHAPE;
+    if (!kernel)
+        return QUARTZ_ERR_NULL;
+    const quartz::WideShape w = quartz::wide_shape(
+        (quartz::LayerKind)layer,
+        {M, N, K, lzs_group, epilogue == QUARTZ_EPI_GELU_TANH, split != 0, blocks});
+    if (w.tr > 0) {
+        const int32_t wide[5] = {QUARTZ_KERNEL_WIDE, 32 * w.tr, 32 * w.wn, 8 / w.wn, 0};
+        std::copy(wide, wide + 5, kernel);
+        return QUARTZ_OK;
+    }
+    const quartz::GemmSchedule s = conv ? quartz::gemm_schedule(M, N, K, blocks, split != 0)
+                                        : quartz::linear_schedule(M, N, K, blocks, split != 0);
+    if (s.blocks <= 0)
+        return QUARTZ_ERR_SHAPE;
+    const int32_t other[5] = {conv ? QUARTZ_KERNEL_GEMM : QUARTZ_KERNEL_LINEAR, conv ? 256 : 128,
+                              conv ? 128 : 256, 1, s.sk_tiles > 0};
+    std::copy(other, other + 5, kernel);
+    return QUARTZ_OK;
 }
 
 quartz_status quartz_w4a4_gemm_i32(const uint8_t* codes, const uint8_t* flags,

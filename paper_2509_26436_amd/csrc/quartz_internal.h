@@ -117,6 +117,12 @@ struct AttnGeom {
     float scale;
 };
 
+// Tile of the wide kernel (w4a4_wide_kernel.h): tr x 32 rows by wn x 32
+// columns; tr = 0: the layer runs its other kernel.
+struct WideShape {
+    int tr, wn;
+};
+
 // Arguments of one GEMM launch (see the kernel template in w4a4_gemm_kernel.h).
 struct GemmLaunch {
     const uint8_t* codes;
@@ -138,28 +144,32 @@ struct GemmLaunch {
     const int16_t* wsums;
     ConvGeom conv;            // implicit 3 x 3 convolution only
     AttnGeom attn;            // attention products only
+    WideShape wide;           // of the layers that wide_shape is asked about
 };
 
 // One output mode each (w4a4_gemm_<mode>.hip).
 hipError_t launch_linear(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_linear_static(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_linear_asym(const GemmLaunch& a, hipStream_t stream);
-// The same layers, and the convolutions, on the wide kernel
-// (w4a4_wide_kernel.h: tiles of tr x 32 rows by wn x 32 columns, no workspace).
-// wide_shape returns the tile with which it is expected to beat
-// w4a4_linear's schedule `lin` (tr = 0: none).
-enum class WideMode { kPlain = 0, kStatic = 1, kAsym = 2 };
-struct WideShape {
-    int tr, wn;
+// The same layers, and the convolutions, on the wide kernel (no workspace):
+// wide_shape returns the tile with which it is expected to beat the layer's
+// other kernel, w4a4_linear or, for a convolution, w4a4_gemm (tr = 0: none).
+// split: that kernel may cut tiles along K; blocks: its persistent grid, and
+// the compute units.  Host only.
+enum class LayerKind { kLinear = 0, kQuantized = 1, kStatic = 2, kAsym = 3, kConv = 4, kConvStatic = 5 };
+struct LayerShape {
+    int64_t M, N, K;
+    int lzs_group;
+    bool gelu, split;
+    int blocks;
 };
-WideShape wide_shape(int64_t M, int64_t N, int64_t K, WideMode mode, const GemmSchedule& lin,
-                     bool conv = false);
-GemmSchedule wide_schedule(const GemmLaunch& a, const WideShape& w);
-hipError_t launch_wide(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
-hipError_t launch_wide_static(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
-hipError_t launch_wide_asym(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
-hipError_t launch_wide_conv(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
-hipError_t launch_wide_conv_static(const GemmLaunch& a, const WideShape& w, hipStream_t stream);
+WideShape wide_shape(LayerKind kind, const LayerShape& s);
+GemmSchedule wide_schedule(const GemmLaunch& a);
+hipError_t launch_wide(const GemmLaunch& a, hipStream_t stream);
+hipError_t launch_wide_static(const GemmLaunch& a, hipStream_t stream);
+hipError_t launch_wide_asym(const GemmLaunch& a, hipStream_t stream);
+hipError_t launch_wide_conv(const GemmLaunch& a, hipStream_t stream);
+hipError_t launch_wide_conv_static(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_gemm_i32(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_gemm_conv(const GemmLaunch& a, hipStream_t stream);
 hipError_t launch_gemm_conv_static(const GemmLaunch& a, hipStream_t stream);

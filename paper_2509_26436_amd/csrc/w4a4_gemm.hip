@@ -96,6 +96,14 @@ static void split_workspace(const GemmSchedule& sch, void* workspace, uint32_t*&
                 : nullptr;
 }
 
+// The wide kernel's tile for a layer, or the kernel of `sch` (w4a4_linear.hip,
+// w4a4_linear_asym.hip: linear_schedule; the convolutions: gemm_schedule).
+static WideShape layer_tile(LayerKind kind, const GemmLaunch& a)
+{
+    return wide_shape(kind, {a.M, a.N, a.K, a.lzs_group, a.epilogue == 1, a.counters != nullptr,
+                             linear_resident_blocks()});
+}
+
 hipError_t launch_w4a4_linear(const uint8_t* codes, const uint8_t* flags,
                               const uint16_t* scales, const uint8_t* w_packed,
                               const uint16_t* bias, uint16_t* y, int64_t M, int64_t N, int64_t K,
@@ -107,8 +115,7 @@ hipError_t launch_w4a4_linear(const uint8_t* codes, const uint8_t* flags,
     GemmLaunch a{codes, flags, scales, w_packed, bias, y, nullptr, M, N, K, ldy, lzs_group,
                  epilogue, sch, nullptr, nullptr, qout, 0.0f};
     split_workspace(sch, workspace, a.counters, a.slots);
-    // the kernel of w4a4_linear.hip (tiles of 128 x 256, schedule from
-    // linear_schedule), bf16 or quantized output
+    a.wide = layer_tile(qout.codes ? LayerKind::kQuantized : LayerKind::kLinear, a);
     return launch_linear(a, stream);
 }
 
@@ -123,7 +130,7 @@ hipError_t launch_w4a4_linear_static(const uint8_t* codes, const uint8_t* flags,
     GemmLaunch a{codes, flags, nullptr, w_packed, bias, y, nullptr, M, N, K, ldy, lzs_group,
                  epilogue, sch, nullptr, nullptr, QuantOut{}, act_scale};
     split_workspace(sch, workspace, a.counters, a.slots);
-    // the kernel of w4a4_linear.hip (schedule from linear_schedule)
+    a.wide = layer_tile(LayerKind::kStatic, a);
     return launch_linear_static(a, stream);
 }
 
@@ -139,7 +146,7 @@ hipError_t launch_w4a4_linear_asym(const uint8_t* codes, const uint8_t* flags,
     GemmLaunch a{codes, flags, scales, w_packed, bias, y, nullptr, M, N, K, ldy, lzs_group,
                  epilogue, sch, nullptr, nullptr, QuantOut{}, 0.0f, zeros, wsums};
     split_workspace(sch, workspace, a.counters, a.slots);
-    // the kernel of w4a4_linear_asym.hip (schedule from linear_schedule)
+    a.wide = layer_tile(LayerKind::kAsym, a);
     return launch_linear_asym(a, stream);
 }
 
@@ -159,6 +166,7 @@ hipError_t launch_w4a4_conv3x3(const uint8_t* codes, const uint8_t* flags,
     GemmLaunch a{codes, flags, scales, w_packed, bias, y, nullptr, M, N, 9 * C, ldy, lzs_group,
                  epilogue, sch, nullptr, nullptr, QuantOut{}, act_scale, nullptr, nullptr, conv};
     split_workspace(sch, workspace, a.counters, a.slots);
+    a.wide = layer_tile(scales ? LayerKind::kConv : LayerKind::kConvStatic, a);
     return scales ? launch_gemm_conv(a, stream) : launch_gemm_conv_static(a, stream);
 }
 

@@ -34,16 +34,16 @@ int linear_resident_blocks()
 
 hipError_t launch_linear(const GemmLaunch& a, hipStream_t stream)
 {
-    if (const WideShape w = wide_shape(a.M, a.N, a.K, WideMode::kPlain, a.sch); w.tr > 0)
-        return launch_wide(a, w, stream);
+    if (a.wide.tr > 0)
+        return launch_wide(a, stream);
     return a.qout.codes ? launch_linear_mode<false, true>(a, stream)
                         : launch_linear_mode<false, false>(a, stream);
 }
 
 hipError_t launch_linear_static(const GemmLaunch& a, hipStream_t stream)
 {
-    if (const WideShape w = wide_shape(a.M, a.N, a.K, WideMode::kStatic, a.sch); w.tr > 0)
-        return launch_wide_static(a, w, stream);
+    if (a.wide.tr > 0)
+        return launch_wide_static(a, stream);
     return launch_linear_mode<true, false>(a, stream);
 }
 

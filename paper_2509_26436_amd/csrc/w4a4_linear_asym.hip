@@ -7,8 +7,8 @@ namespace quartz {
 
 hipError_t launch_linear_asym(const GemmLaunch& a, hipStream_t stream)
 {
-    if (const WideShape w = wide_shape(a.M, a.N, a.K, WideMode::kAsym, a.sch); w.tr > 0)
-        return launch_wide_asym(a, w, stream);
+    if (a.wide.tr > 0)
+        return launch_wide_asym(a, stream);
     return launch_linear_mode<false, false, true>(a, stream);
 }
 

@@ -57,15 +57,26 @@ constexpr Costs kCosts[3] = {
      {5.89f, 0.578f, 0.740f, 1.96f, 18.1f, 0.224f}},
 };
 constexpr float kMargin = 0.97f;
-// The static convolution's gather weighs more on w4a4_gemm, whose waves all
-// multiply, than on the wide kernel: 16384 x 2880 -> 320 31.1 us against 22.6
-// for the linear layer there, 26.9 against 24.6 here.
+// The per-group convolution takes the tile that the linear layer takes on the
+// im2col matrix (with or without its split, as a workspace is there): both
+// then add the groups in the same order, so their outputs are equal bit for
+// bit.  (4096 x 5760 -> 640: 37 us against 44 on w4a4_gemm; 9216 x 5760 ->
+// 1280: 88 against 104; where the linear layer stays with w4a4_linear, w4a4_gemm
+// wins here too: 16384 x 2880 -> 320 34 against 38.)  The static one's sums
+// are exact integers in any order (26 us against 41; 53 against 86; 27 against
+// 31).  Its gather weighs more on w4a4_gemm, whose waves all multiply, than on
+// the wide kernel: 16384 x 2880 -> 320 31.1 us against 22.6 for the linear
+// layer there, 26.9 against 24.6 here.
 constexpr float kConvStatic = 1.2f;
 
 }  // namespace
 
-WideShape wide_shape(int64_t M, int64_t N, int64_t K, WideMode mode, const GemmSchedule& lin, bool conv)
+WideShape wide_shape(LayerKind kind, const LayerShape& s)
 {
+    const int64_t M = s.M, N = s.N, K = s.K;
+    const bool conv = kind == LayerKind::kConv || kind == LayerKind::kConvStatic;
+    const bool asym = kind == LayerKind::kAsym, is_static = kind == LayerKind::kStatic || kind == LayerKind::kConvStatic;
+    const GemmSchedule lin = linear_schedule(M, N, K, s.blocks, s.split);
     const int64_t G = K / kGroup;
     const int64_t panels = (N + kPanel - 1) / kPanel;
     // the kernel's offsets are 32-bit: every array's range ends below 2^30,
@@ -74,8 +85,8 @@ WideShape wide_shape(int64_t M, int64_t N, int64_t K, WideMode mode, const GemmS
     constexpr int64_t kMost = int64_t(1) << 30;
     if (M * G * 32 > kMost || panels * G * kChunkBytes > kMost || N * G * 2 > kMost || M > (int64_t(1) << 22))
         return {0, 0};
-    const int64_t blocks = device_compute_units();
-    const Costs& k = kCosts[(int)mode];
+    const int64_t blocks = s.blocks;
+    const Costs& k = kCosts[asym ? 2 : is_static ? 1 : 0];
     auto rounds = [&](int64_t tiles) { return (float)((tiles + blocks - 1) / blocks); };
     auto load = [&](int64_t tiles) { return (float)tiles / (float)blocks; };
     const int64_t lin_tiles = ((M + 127) / 128) * ((N + 255) / 256);
@@ -87,7 +98,7 @@ WideShape wide_shape(int64_t M, int64_t N, int64_t K, WideMode mode, const GemmS
         best = k.lin.c + load(lin_tiles) * groups * k.lin.gs + k.lin.ts;
     else
         best = k.lin.c + (float)lin.sk_q * k.lin.gs + 10.2f + 0.093f * (float)lin_tiles;
-    best *= conv && mode == WideMode::kStatic ? kConvStatic : kMargin;
+    best *= conv && is_static ? kConvStatic : kMargin;
     WideShape w{0, 0};
     auto consider = [&](const WideCost& c, int tr, int wn) {
         const int64_t teams = kWideWaves / wn;
@@ -99,7 +110,7 @@ WideShape wide_shape(int64_t M, int64_t N, int64_t K, WideMode mode, const GemmS
             w = {tr, wn};
         }
     };
-    for (int tr = 4; tr <= (mode == WideMode::kAsym ? 7 : 8); ++tr)
+    for (int tr = 4; tr <= (asym ? 7 : 8); ++tr)
         consider(k.one, tr, 8);
     for (int tr = 2; tr <= 4; ++tr)
         consider(k.two, tr, 4);
@@ -107,15 +118,15 @@ WideShape wide_shape(int64_t M, int64_t N, int64_t K, WideMode mode, const GemmS
     return w;
 }
 
-GemmSchedule wide_schedule(const GemmLaunch& a, const WideShape& w)
+GemmSchedule wide_schedule(const GemmLaunch& a)
 {
-    return gemm_schedule_tiles(a.M, a.N, a.K, device_compute_units(), false, 32 * w.tr, 32 * w.wn);
+    return gemm_schedule_tiles(a.M, a.N, a.K, device_compute_units(), false, 32 * a.wide.tr, 32 * a.wide.wn);
 }
 
-hipError_t launch_wide(const GemmLaunch& a, const WideShape& w, hipStream_t stream)
+hipError_t launch_wide(const GemmLaunch& a, hipStream_t stream)
 {
-    return a.qout.codes ? launch_wide_mode<false, true, false, false>(a, w, stream)
-                        : launch_wide_mode<false, false, false, false>(a, w, stream);
+    return a.qout.codes ? launch_wide_mode<false, true, false, false>(a, stream)
+                        : launch_wide_mode<false, false, false, false>(a, stream);
 }
 
 }  // namespace quartz

@@ -4,14 +4,14 @@
 
 namespace quartz {
 
-hipError_t launch_wide_conv(const GemmLaunch& a, const WideShape& w, hipStream_t stream)
+hipError_t launch_wide_conv(const GemmLaunch& a, hipStream_t stream)
 {
-    return launch_wide_mode<false, false, false, true>(a, w, stream);
+    return launch_wide_mode<false, false, false, true>(a, stream);
 }
 
-hipError_t launch_wide_conv_static(const GemmLaunch& a, const WideShape& w, hipStream_t stream)
+hipError_t launch_wide_conv_static(const GemmLaunch& a, hipStream_t stream)
 {
-    return launch_wide_mode<true, false, false, true>(a, w, stream);
+    return launch_wide_mode<true, false, false, true>(a, stream);
 }
 
 }  // namespace quartz

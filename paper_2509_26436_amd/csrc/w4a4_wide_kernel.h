@@ -620,9 +620,10 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2,
 }
 
 template <bool STATIC, bool QOUT, bool ASYM, bool CONV>
-hipError_t launch_wide_mode(const GemmLaunch& a, const WideShape& w, hipStream_t stream)
+hipError_t launch_wide_mode(const GemmLaunch& a, hipStream_t stream)
 {
-    const GemmSchedule sch = wide_schedule(a, w);
+    const WideShape& w = a.wide;
+    const GemmSchedule sch = wide_schedule(a);
     const dim3 grid((unsigned)sch.blocks), block(kWideThreads);
     auto go = [&](auto gs, auto tr, auto wn) {
         w4a4_wide_kernel<decltype(gs)::value, decltype(tr)::value, decltype(wn)::value, STATIC, QOUT, ASYM, CONV>

@@ -4,14 +4,14 @@
 
 namespace quartz {
 
-hipError_t launch_wide_static(const GemmLaunch& a, const WideShape& w, hipStream_t stream)
+hipError_t launch_wide_static(const GemmLaunch& a, hipStream_t stream)
 {
-    return launch_wide_mode<true, false, false, false>(a, w, stream);
+    return launch_wide_mode<true, false, false, false>(a, stream);
 }
 
-hipError_t launch_wide_asym(const GemmLaunch& a, const WideShape& w, hipStream_t stream)
+hipError_t launch_wide_asym(const GemmLaunch& a, hipStream_t stream)
 {
-    return launch_wide_mode<false, false, true, false>(a, w, stream);
+    return launch_wide_mode<false, false, true, false>(a, stream);
 }
 
 }  // namespace quartz
