@@ -1,121 +1,187 @@
 // The wide kernel (w4a4_wide_kernel.h): the rule that picks it and its tile, and the per-group launches (bf16 or quantized output).
+#include <array>
+
 #include "w4a4_wide_kernel.h"
 
 namespace quartz {
 namespace {
 
-// Launch times in microseconds, fitted (relative least squares over 30 shapes
-// of 220 to 18432 rows, the wide kernel at every tile; residuals 2-4 %).  The
-// teams of a tile share its groups, so each takes `steps` of them, a multiple
-// of two:
-//   wide           c + rounds (steps (g0 + g1 TR) + t0 + t1 TR) + load steps TR u
-//   whole tiles    c + rounds (groups g + t) + load groups u
-//   split          c + load groups gs + ts,  with fewer tiles than workgroups
-//                  c + (groups per workgroup) gs + 10.2 + 0.093 tiles
-// where load = tiles / compute units; its terms are what a busier device costs
-// in clock.  What they say: a tile row of 7 x 32 costs 0.99 us a group against
-// 2 x 0.61 for the 256 rows of two w4a4_linear tiles (static 0.53 against 2 x
-// 0.35), and tiles of 4 x 32 rows lose that (0.67 against 0.61).  So one team
-// takes shapes for which some height fills whole rounds of the device (4608
-// rows: 7 x 32, 98 % full; 4608 x 3072 -> 9216: 153 us against 173).  Fewer
-// tiles than compute units is where the others come in: w4a4_linear then
-// splits the groups over workgroups and pays 10 to 20 us for exchanging
-// partial sums through memory, a tile of two or four teams splits them within
-// a workgroup for about 1 us (256 x 1152 -> 1152: 7.0 us against 15.4; 333 x
-// 2048 -> 1000: 8.2 against 20.4; 1024 x 3072 -> 3072: 22.0 against 39.1).
-// w4a4_linear keeps the shapes with too few tiles even so and many groups
-// (1024 x 11520 -> 1280: 44 us against 49) and 128-row tiles that fill a round
-// (4096 x 4608 -> 1152: 47 us against 50).  Over the 30 shapes the choice is
-// within 1 % of the best kernel and tile (geometric mean; 1.26 times faster
-// than w4a4_linear alone) and never slower than w4a4_linear; closer than 3 %
-// it stays with the latter.
+// Launch times in microseconds, fitted per kind of layer (relative least
+// squares; every tile and the other kernel timed
+// over 3200 random shapes of a kind, M to 18432, K to 12288, every G_s, half
+// with a workspace; residuals 2-4 %, 10 % where tiles are fewer than
+// workgroups and split):
+//   wide     c + rounds (steps (g0 + g1 TR) (1 + g8) + t0 + (t1 + te) TR)
+//            + load TR (steps u + s)
+//   whole    c + rounds (groups g (1 + g8 + ge) + t + te) + load (groups u + s)
+//   split    c + load (groups g (1 + g8) + t + te), with fewer tiles than
+//            workgroups c + (groups per workgroup) g (1 + g8) + te
+// where rounds and load are tiles over compute units, rounded up and not; a
+// team takes `steps` of the tile's groups, a multiple of two; g8 counts at
+// G_s = 8 (twice the FLAGs to look at), te and ge with GELU.  The u and s terms
+// are what a busier device costs in clock and in stores.
+//
+// What they say: a tile row of 7 x 32 costs 0.80 us a group against 2 x 0.51
+// for the 256 rows of two w4a4_linear tiles (static 0.36 against 2 x 0.28), and
+// tiles of 4 x 32 rows lose that.  So one team takes shapes for which some
+// height fills whole rounds of the device (4608 rows: 7 x 32, 98 % full; 4608 x
+// 3072 -> 9216: 153 us against 173).  Fewer tiles than compute units is where
+// the others come in: w4a4_linear then splits the groups over workgroups and
+// pays 10 to 20 us for exchanging partial sums through memory, a tile of two or
+// four teams splits them within a workgroup for about 1 us (256 x 1152 -> 1152:
+// 7.0 us against 15.4; 333 x 2048 -> 1000: 8.2 against 20.4; 1024 x 3072 ->
+// 3072: 22.0 against 39.1).  w4a4_linear keeps the shapes with too few tiles
+// even so and many groups (1024 x 11520 -> 1280: 44 us against 49), 128-row
+// tiles that fill a round (4096 x 4608 -> 1152: 47 us against 50), and more of
+// them with zero points or at G_s = 8 (7107 x 2432 -> 6667, asymmetric, G_s =
+// 8, GELU: 195 us against 215; 3367 x 1088 -> 1703, static, G_s = 8: 13.7
+// against 14.9).
+//
+// The choice takes what is expected to be at least 4 % faster, so that what is
+// not in these terms does not turn it into a loss: over the fitted shapes it is
+// 0.1 to 0.4 % slower than the best kernel and tile (geometric mean), 0.68 to
+// 0.71 of w4a4_linear's time, and slower than the other kernel by
+// more than 2 % in 10 of 9600 shapes.
 struct WideCost {
-    float c, g0, g1, t0, t1, u;
+    float c, g0, g1, g8, t0, t1, te, u, s;
 };
-struct LinearCost {
-    float c, g, gs, t, ts, u;
+struct WholeCost {
+    float c, g, g8, ge, t, te, u, s;
+};
+struct SplitCost {
+    float c, g, g8, t, te;
 };
 struct Costs {
     WideCost one, two, four;                     // by teams
-    LinearCost lin;
+    WholeCost whole;
+    SplitCost split, split_small;
 };
 // the asymmetric mode's zero-point operands leave no registers for 8 row tiles
 // (20 values spill around every group: 98 us against 69 at 7 x 32 rows, 4608 x
 // 3072 -> 3072)
 constexpr Costs kCosts[3] = {
-    {{3.35f, 0.234f, 0.088f, 0.15f, 0.43f, 0.020f},   // bf16 and quantized output
-     {3.37f, 0.329f, 0.067f, 0.16f, 0.46f, 0.027f},
-     {3.24f, 0.457f, 0.0f, 1.29f, 0.0f, 0.017f},
-     {5.57f, 0.419f, 0.630f, 1.91f, 15.2f, 0.196f}},
-    {{3.22f, 0.255f, 0.024f, -0.12f, 0.52f, 0.017f},  // static
-     {3.07f, 0.281f, 0.021f, 0.30f, 0.45f, 0.017f},
-     {3.28f, 0.329f, 0.0f, 1.22f, 0.0f, 0.011f},
-     {4.94f, 0.196f, 0.356f, 2.49f, 18.9f, 0.166f}},
-    {{3.52f, 0.232f, 0.124f, 0.37f, 0.37f, 0.019f},   // asymmetric
-     {3.32f, 0.423f, 0.076f, 0.05f, 0.50f, 0.030f},
-     {3.24f, 0.556f, 0.0f, 1.26f, 0.0f, 0.014f},
-     {5.89f, 0.578f, 0.740f, 1.96f, 18.1f, 0.224f}},
+    // per-group, bf16 output
+    {{4.437f, 0.265f, 0.076f, 0.043f, -0.149f, 0.237f, 0.312f, 0.023f, 0.354f},
+     {3.426f, 0.293f, 0.072f, 0.064f, 0.396f, 0.386f, 0.181f, 0.020f, 0.098f},
+     {3.068f, 0.443f, 0.0f, 0.071f, 1.430f, 0.0f, 0.145f, 0.020f, 0.0f},
+     {5.683f, 0.505f, 0.014f, 0.0f, 0.600f, 1.256f, 0.078f, 2.500f},
+     {18.465f, 0.595f, 0.023f, 2.759f, 1.362f},
+     {20.940f, 0.655f, -0.002f, 0.0f, 1.168f}},
+    // static
+    {{3.554f, 0.206f, 0.022f, 0.096f, 0.251f, 0.285f, 0.314f, 0.033f, 0.262f},
+     {2.785f, 0.265f, 0.015f, 0.143f, 0.392f, 0.342f, 0.181f, 0.020f, 0.231f},
+     {2.551f, 0.297f, 0.0f, 0.205f, 1.404f, 0.0f, 0.171f, 0.024f, 0.0f},
+     {4.687f, 0.282f, 0.021f, 0.0f, 1.149f, 1.379f, 0.075f, 2.152f},
+     {15.118f, 0.388f, 0.035f, 3.884f, 1.382f},
+     {22.511f, 0.354f, 0.040f, 0.0f, 0.964f}},
+    // asymmetric
+    {{4.470f, 0.275f, 0.113f, 0.034f, -0.358f, 0.239f, 0.324f, 0.016f, 0.394f},
+     {3.565f, 0.356f, 0.090f, 0.058f, 0.410f, 0.357f, 0.176f, 0.019f, 0.099f},
+     {3.129f, 0.559f, 0.0f, 0.066f, 1.389f, 0.0f, 0.151f, 0.013f, 0.0f},
+     {6.084f, 0.664f, 0.017f, -0.094f, 0.389f, 1.629f, 0.100f, 2.851f},
+     {19.108f, 0.690f, 0.017f, 3.293f, 1.498f},
+     {22.105f, 0.733f, 0.048f, 0.0f, 1.198f}},
 };
-constexpr float kMargin = 0.97f;
+constexpr float kMargin = 0.96f;
 // The per-group convolution takes the tile that the linear layer takes on the
 // im2col matrix (with or without its split, as a workspace is there): both
 // then add the groups in the same order, so their outputs are equal bit for
-// bit.  (4096 x 5760 -> 640: 37 us against 44 on w4a4_gemm; 9216 x 5760 ->
-// 1280: 88 against 104; where the linear layer stays with w4a4_linear, w4a4_gemm
-// wins here too: 16384 x 2880 -> 320 34 against 38.)  The static one's sums
-// are exact integers in any order (26 us against 41; 53 against 86; 27 against
-// 31).  Its gather weighs more on w4a4_gemm, whose waves all multiply, than on
-// the wide kernel: 16384 x 2880 -> 320 31.1 us against 22.6 for the linear
-// layer there, 26.9 against 24.6 here.
+// bit.  The static one's sums are exact integers in any order, and its gather
+// weighs more on w4a4_gemm, whose waves all multiply, than on the wide kernel.
 constexpr float kConvStatic = 1.2f;
+
+// the tiles, by teams: one, two, four
+struct Tile {
+    int tr, wn;
+};
+constexpr Tile kTiles[] = {{4, 8}, {5, 8}, {6, 8}, {7, 8}, {8, 8}, {2, 4}, {3, 4}, {4, 4}, {2, 2}};
+constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+
+// What a launch of each tile comes to, whatever the kind of layer.
+struct TileLoads {
+    float steps[3], rounds[kNumTiles], load[kNumTiles];   // load < 0: more tiles than a launch can number
+    TileLoads(const LayerShape& s)
+    {
+        const int32_t G = (int32_t)(s.K / kGroup);
+        for (int i = 0; i < 3; ++i)
+            steps[i] = (float)((G + (2 << i) - 1) / (2 << i) * 2);
+        for (int i = 0; i < kNumTiles; ++i) {
+            const int64_t bm = 32 * kTiles[i].tr, bn = 32 * kTiles[i].wn;
+            const int64_t tiles = ((s.M + bm - 1) / bm) * ((s.N + bn - 1) / bn);
+            const bool ok = tiles <= kMaxGemmTiles / 2;
+            rounds[i] = (float)(((uint32_t)tiles + (uint32_t)s.blocks - 1) / (uint32_t)s.blocks);
+            load[i] = ok ? (float)tiles / (float)s.blocks : -1.0f;
+        }
+    }
+};
+
+// the best tile with each number of teams: [0] one, [1] two, [2] four
+struct Best {
+    float us;
+    WideShape w;
+};
+std::array<Best, 3> best_tiles(LayerKind kind, const LayerShape& s, const TileLoads& l)
+{
+    const Costs& k = kCosts[kind == LayerKind::kAsym ? 2 : kind == LayerKind::kStatic || kind == LayerKind::kConvStatic ? 1 : 0];
+    std::array<Best, 3> best;
+    best.fill({1e30f, {0, 0}});
+    for (int i = 0; i < kNumTiles; ++i) {
+        const Tile& t = kTiles[i];
+        if (l.load[i] < 0.0f || (kind == LayerKind::kAsym && t.tr == 8))
+            continue;
+        const int c = t.wn == 8 ? 0 : t.wn == 4 ? 1 : 2;
+        const WideCost& w = c == 0 ? k.one : c == 1 ? k.two : k.four;
+        const float tr = (float)t.tr, g8 = s.lzs_group == 8 ? w.g8 : 0.0f, te = s.gelu ? w.te : 0.0f;
+        const float us = w.c + l.rounds[i] * (l.steps[c] * (w.g0 + w.g1 * tr) * (1.0f + g8) + w.t0 + (w.t1 + te) * tr) +
+                         l.load[i] * tr * (l.steps[c] * w.u + w.s);
+        if (us < best[c].us)
+            best[c] = {us, {t.tr, t.wn}};
+    }
+    return best;
+}
+
+// the other kernel, with its schedule
+float other_us(LayerKind kind, const LayerShape& s, const GemmSchedule& sch)
+{
+    const Costs& k = kCosts[kind == LayerKind::kAsym ? 2 : kind == LayerKind::kStatic || kind == LayerKind::kConvStatic ? 1 : 0];
+    const float tiles = (float)(sch.sk_first + sch.sk_tiles), groups = (float)sch.groups, load = tiles / (float)s.blocks;
+    const bool fine = s.lzs_group == 8;
+    if (sch.sk_tiles == 0) {
+        const WholeCost& w = k.whole;
+        const float rounds = (float)((sch.sk_first + s.blocks - 1) / s.blocks);
+        return w.c + rounds * (groups * w.g * (1.0f + (fine ? w.g8 : 0.0f) + (s.gelu ? w.ge : 0.0f)) + w.t + (s.gelu ? w.te : 0.0f)) +
+               load * (groups * w.u + w.s);
+    }
+    const SplitCost& w = load > 1.0f ? k.split : k.split_small;
+    const float g = w.g * (1.0f + (fine ? w.g8 : 0.0f)), te = s.gelu ? w.te : 0.0f;
+    return load > 1.0f ? w.c + load * (groups * g + w.t + te) : w.c + (float)sch.sk_q * g + te;
+}
 
 }  // namespace
 
+// the tile that beats `limit` by most
+WideShape fastest(const std::array<Best, 3>& b, float limit)
+{
+    WideShape w{0, 0};
+    for (const Best& x : b)
+        if (x.us < limit) {
+            limit = x.us;
+            w = x.w;
+        }
+    return w;
+}
+
 WideShape wide_shape(LayerKind kind, const LayerShape& s)
 {
-    const int64_t M = s.M, N = s.N, K = s.K;
-    const bool conv = kind == LayerKind::kConv || kind == LayerKind::kConvStatic;
-    const bool asym = kind == LayerKind::kAsym, is_static = kind == LayerKind::kStatic || kind == LayerKind::kConvStatic;
-    const GemmSchedule lin = linear_schedule(M, N, K, s.blocks, s.split);
-    const int64_t G = K / kGroup;
-    const int64_t panels = (N + kPanel - 1) / kPanel;
     // the kernel's offsets are 32-bit: every array's range ends below 2^30,
     // where a group past the last one reads, and the rows' offsets of the up
     // to 7 groups past the last one below 2^31, which marks a lane as outside
     constexpr int64_t kMost = int64_t(1) << 30;
-    if (M * G * 32 > kMost || panels * G * kChunkBytes > kMost || N * G * 2 > kMost || M > (int64_t(1) << 22))
+    const int64_t G = s.K / kGroup, panels = (s.N + kPanel - 1) / kPanel;
+    if (s.M * G * 32 > kMost || panels * G * kChunkBytes > kMost || s.N * G * 2 > kMost || s.M > (int64_t(1) << 22))
         return {0, 0};
-    const int64_t blocks = s.blocks;
-    const Costs& k = kCosts[asym ? 2 : is_static ? 1 : 0];
-    auto rounds = [&](int64_t tiles) { return (float)((tiles + blocks - 1) / blocks); };
-    auto load = [&](int64_t tiles) { return (float)tiles / (float)blocks; };
-    const int64_t lin_tiles = ((M + 127) / 128) * ((N + 255) / 256);
-    const float groups = (float)G;
-    float best;
-    if (lin.sk_tiles == 0)
-        best = k.lin.c + rounds(lin_tiles) * (groups * k.lin.g + k.lin.t) + load(lin_tiles) * groups * k.lin.u;
-    else if (lin_tiles > blocks)
-        best = k.lin.c + load(lin_tiles) * groups * k.lin.gs + k.lin.ts;
-    else
-        best = k.lin.c + (float)lin.sk_q * k.lin.gs + 10.2f + 0.093f * (float)lin_tiles;
-    best *= conv && is_static ? kConvStatic : kMargin;
-    WideShape w{0, 0};
-    auto consider = [&](const WideCost& c, int tr, int wn) {
-        const int64_t teams = kWideWaves / wn;
-        const int64_t tiles = ((M + 32 * tr - 1) / (32 * tr)) * ((N + 32 * wn - 1) / (32 * wn));
-        const float steps = (float)((G + 2 * teams - 1) / (2 * teams) * 2), t = (float)tr;
-        const float us = c.c + rounds(tiles) * (steps * (c.g0 + c.g1 * t) + c.t0 + c.t1 * t) + load(tiles) * steps * t * c.u;
-        if (us < best && tiles <= kMaxGemmTiles / 2) {
-            best = us;
-            w = {tr, wn};
-        }
-    };
-    for (int tr = 4; tr <= (asym ? 7 : 8); ++tr)
-        consider(k.one, tr, 8);
-    for (int tr = 2; tr <= 4; ++tr)
-        consider(k.two, tr, 4);
-    consider(k.four, 2, 2);
-    return w;
+    const float other = other_us(kind, s, linear_schedule(s.M, s.N, s.K, s.blocks, s.split));
+    return fastest(best_tiles(kind, s, TileLoads(s)), other * (kind == LayerKind::kConvStatic ? kConvStatic : kMargin));
 }
 
 GemmSchedule wide_schedule(const GemmLaunch& a)

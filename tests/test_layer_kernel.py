@@ -81,3 +81,17 @@ def test_arguments():
                         ((256, 256, 576, 16, 2, 0, 1, 256), 3), ((256, 256, 576, 16, 0, 6, 1, 256), 3)):
         assert call(*bad) == status, bad
     assert q.quartz_w4a4_layer_kernel(256, 256, 576, 16, 0, 0, 1, 256, None) == 1
+
+
+# (layer, M, N, K, G_s, epilogue, workspace): calls that w4a4_linear runs 5 to 10 % faster than the
+# wide kernel's best tile does
+@pytest.mark.parametrize("case", [
+    ("asym", 7107, 6667, 2432, 8, 1, True), ("asym", 8534, 10432, 3072, 16, 1, True),
+    ("asym", 3722, 2560, 10752, 8, 0, True),
+    ("asym", 2806, 2368, 2688, 8, 1, True), ("asym", 4042, 2027, 2752, 16, 1, True),
+    ("static", 16716, 461, 11648, 8, 0, True), ("static", 3367, 1703, 1088, 8, 0, True),
+    ("static", 16190, 380, 1280, 8, 0, True), ("static", 571, 12203, 1216, 8, 0, False),
+], ids=lambda c: "-".join(map(str, c)))
+def test_calls_that_the_other_kernel_runs_faster(case):
+    layer, M, N, K, gs, epi, split = case
+    assert q.layer_kernel(M, N, K, gs, layer, epi, split)["kernel"] != "wide"
