@@ -11,7 +11,7 @@ namespace {
 // over 3200 random shapes of a kind, M to 18432, K to 12288, every G_s, half
 // with a workspace; residuals 2-4 %, 10 % where tiles are fewer than
 // workgroups and split):
-//   wide     c + rounds (steps (g0 + g1 TR) (1 + g8) + t0 + (t1 + te) TR)
+//   wide     c + rounds (steps (g0 + g1 TR) (1 + g8) + t0 passes + (t1 + te) TR)
 //            + load TR (steps u + s)
 //   whole    c + rounds (groups g (1 + g8 + ge) + t + te) + load (groups u + s)
 //   split    c + load (groups g (1 + g8) + t + te), with fewer tiles than
@@ -37,11 +37,16 @@ namespace {
 // 8, GELU: 195 us against 215; 3367 x 1088 -> 1703, static, G_s = 8: 13.7
 // against 14.9).
 //
+// The quantized output's epilogue weighs 2 us per pass of 128 rows, and 8 row
+// tiles spill 11 or 12 registers there (convolutions 5 or 6 at G_s 8 and 16),
+// which its times include: 5823 x 4608 -> 704 stays with w4a4_linear for both
+// outputs (46.9 us against 50.4 for the quantized one).
+//
 // The choice takes what is expected to be at least 4 % faster, so that what is
 // not in these terms does not turn it into a loss: over the fitted shapes it is
 // 0.1 to 0.4 % slower than the best kernel and tile (geometric mean), 0.68 to
 // 0.71 of w4a4_linear's time, and slower than the other kernel by
-// more than 2 % in 10 of 9600 shapes.
+// more than 2 % in 11 of 12800 shapes.
 struct WideCost {
     float c, g0, g1, g8, t0, t1, te, u, s;
 };
@@ -59,7 +64,7 @@ struct Costs {
 // the asymmetric mode's zero-point operands leave no registers for 8 row tiles
 // (20 values spill around every group: 98 us against 69 at 7 x 32 rows, 4608 x
 // 3072 -> 3072)
-constexpr Costs kCosts[3] = {
+constexpr Costs kCosts[4] = {
     // per-group, bf16 output
     {{4.437f, 0.265f, 0.076f, 0.043f, -0.149f, 0.237f, 0.312f, 0.023f, 0.354f},
      {3.426f, 0.293f, 0.072f, 0.064f, 0.396f, 0.386f, 0.181f, 0.020f, 0.098f},
@@ -67,6 +72,13 @@ constexpr Costs kCosts[3] = {
      {5.683f, 0.505f, 0.014f, 0.0f, 0.600f, 1.256f, 0.078f, 2.500f},
      {18.465f, 0.595f, 0.023f, 2.759f, 1.362f},
      {20.940f, 0.655f, -0.002f, 0.0f, 1.168f}},
+    // quantized output
+    {{3.515f, 0.244f, 0.079f, 0.044f, 1.885f, 0.442f, 0.375f, 0.022f, 0.014f},
+     {3.233f, 0.316f, 0.067f, 0.058f, 1.988f, 0.340f, 0.200f, 0.017f, -0.014f},
+     {3.080f, 0.449f, 0.0f, 0.076f, 2.825f, 0.0f, 0.135f, 0.016f, 0.0f},
+     {4.448f, 0.505f, 0.026f, 0.0f, 3.260f, 1.782f, 0.063f, 0.863f},
+     {17.448f, 0.590f, 0.019f, 3.841f, 1.851f},
+     {23.054f, 0.620f, 0.0f, 0.0f, 0.996f}},
     // static
     {{3.554f, 0.206f, 0.022f, 0.096f, 0.251f, 0.285f, 0.314f, 0.033f, 0.262f},
      {2.785f, 0.265f, 0.015f, 0.143f, 0.392f, 0.342f, 0.181f, 0.020f, 0.231f},
@@ -122,7 +134,7 @@ struct Best {
 };
 std::array<Best, 3> best_tiles(LayerKind kind, const LayerShape& s, const TileLoads& l)
 {
-    const Costs& k = kCosts[kind == LayerKind::kAsym ? 2 : kind == LayerKind::kStatic || kind == LayerKind::kConvStatic ? 1 : 0];
+    const Costs& k = kCosts[kind == LayerKind::kConv ? 0 : kind == LayerKind::kConvStatic ? 2 : (int)kind];
     std::array<Best, 3> best;
     best.fill({1e30f, {0, 0}});
     for (int i = 0; i < kNumTiles; ++i) {
@@ -132,7 +144,9 @@ std::array<Best, 3> best_tiles(LayerKind kind, const LayerShape& s, const TileLo
         const int c = t.wn == 8 ? 0 : t.wn == 4 ? 1 : 2;
         const WideCost& w = c == 0 ? k.one : c == 1 ? k.two : k.four;
         const float tr = (float)t.tr, g8 = s.lzs_group == 8 ? w.g8 : 0.0f, te = s.gelu ? w.te : 0.0f;
-        const float us = w.c + l.rounds[i] * (l.steps[c] * (w.g0 + w.g1 * tr) * (1.0f + g8) + w.t0 + (w.t1 + te) * tr) +
+        // the quantizing epilogue goes through LDS 128 rows at a time
+        const float passes = kind == LayerKind::kQuantized && t.tr > 4 ? 2.0f : 1.0f;
+        const float us = w.c + l.rounds[i] * (l.steps[c] * (w.g0 + w.g1 * tr) * (1.0f + g8) + w.t0 * passes + (w.t1 + te) * tr) +
                          l.load[i] * tr * (l.steps[c] * w.u + w.s);
         if (us < best[c].us)
             best[c] = {us, {t.tr, t.wn}};
@@ -143,7 +157,7 @@ std::array<Best, 3> best_tiles(LayerKind kind, const LayerShape& s, const TileLo
 // the other kernel, with its schedule
 float other_us(LayerKind kind, const LayerShape& s, const GemmSchedule& sch)
 {
-    const Costs& k = kCosts[kind == LayerKind::kAsym ? 2 : kind == LayerKind::kStatic || kind == LayerKind::kConvStatic ? 1 : 0];
+    const Costs& k = kCosts[kind == LayerKind::kConv ? 0 : kind == LayerKind::kConvStatic ? 2 : (int)kind];
     const float tiles = (float)(sch.sk_first + sch.sk_tiles), groups = (float)sch.groups, load = tiles / (float)s.blocks;
     const bool fine = s.lzs_group == 8;
     if (sch.sk_tiles == 0) {
@@ -159,18 +173,13 @@ float other_us(LayerKind kind, const LayerShape& s, const GemmSchedule& sch)
 
 }  // namespace
 
-// the tile that beats `limit` by most
-WideShape fastest(const std::array<Best, 3>& b, float limit)
-{
-    WideShape w{0, 0};
-    for (const Best& x : b)
-        if (x.us < limit) {
-            limit = x.us;
-            w = x.w;
-        }
-    return w;
-}
-
+// The linear layer and its quantized output have to add the groups of an output
+// in one order: the codes are those of the stored bf16 output, bit for bit.
+// The orders are ascending (one team, or w4a4_linear without a split), by two
+// teams, by four, and that of w4a4_linear's split.  One that w4a4_linear does
+// not have is open when some tile of it beats w4a4_linear for both outputs
+// (14720 x 512 -> 384: two teams would take 14.3 us for the quantized one
+// against 12.9), and the bf16 output's times pick among the open ones.
 WideShape wide_shape(LayerKind kind, const LayerShape& s)
 {
     // the kernel's offsets are 32-bit: every array's range ends below 2^30,
@@ -180,8 +189,33 @@ WideShape wide_shape(LayerKind kind, const LayerShape& s)
     const int64_t G = s.K / kGroup, panels = (s.N + kPanel - 1) / kPanel;
     if (s.M * G * 32 > kMost || panels * G * kChunkBytes > kMost || s.N * G * 2 > kMost || s.M > (int64_t(1) << 22))
         return {0, 0};
-    const float other = other_us(kind, s, linear_schedule(s.M, s.N, s.K, s.blocks, s.split));
-    return fastest(best_tiles(kind, s, TileLoads(s)), other * (kind == LayerKind::kConvStatic ? kConvStatic : kMargin));
+    const TileLoads loads(s);
+    const LayerKind layer = kind == LayerKind::kQuantized || kind == LayerKind::kConv ? LayerKind::kLinear : kind;
+    const GemmSchedule lin = linear_schedule(s.M, s.N, s.K, s.blocks, s.split);
+    const bool whole = lin.sk_tiles == 0;
+    const std::array<Best, 3> own = best_tiles(kind, s, loads);
+    const float own_other = other_us(kind, s, lin) * (kind == LayerKind::kConvStatic ? kConvStatic : kMargin);
+    const std::array<Best, 3> y = kind == layer ? own : best_tiles(layer, s, loads);
+    const float y_other = kind == layer ? own_other : kMargin * other_us(layer, s, lin);
+    bool open[3];
+    for (int c = 0; c < 3; ++c)
+        open[c] = y[c].us < y_other;
+    if (layer == LayerKind::kLinear && s.N % kGroup == 0) {
+        const std::array<Best, 3> b = best_tiles(LayerKind::kQuantized, s, loads);
+        const float limit = kMargin * other_us(LayerKind::kQuantized, s, lin);
+        for (int c = 0; c < 3; ++c)
+            open[c] = open[c] && b[c].us < limit;
+    }
+    int order = whole ? 0 : -1;                  // w4a4_linear's
+    float best = whole ? std::min(y[0].us, y_other) : y_other;
+    for (int c = whole ? 1 : 0; c < 3; ++c)
+        if (open[c] && y[c].us < best) {
+            best = y[c].us;
+            order = c;
+        }
+    if (order < 0 || (order == 0 && whole && own[0].us >= own_other))
+        return {0, 0};
+    return own[order].w;
 }
 
 GemmSchedule wide_schedule(const GemmLaunch& a)

@@ -95,3 +95,16 @@ def test_arguments():
 def test_calls_that_the_other_kernel_runs_faster(case):
     layer, M, N, K, gs, epi, split = case
     assert q.layer_kernel(M, N, K, gs, layer, epi, split)["kernel"] != "wide"
+
+
+# the same where the wide kernel would win for the bf16 output alone
+@pytest.mark.parametrize("case", [
+    (5823, 704, 4608, 16, 0, True), (3965, 5824, 11200, 8, 0, True), (14894, 1088, 5376, 8, 1, True),
+    (648, 5696, 1152, 8, 0, True), (700, 11264, 6912, 16, 0, True), (15199, 1472, 11264, 8, 0, True),
+    (12882, 320, 704, 64, 0, False),
+], ids=lambda c: "-".join(map(str, c)))
+def test_quantized_outputs_that_the_other_kernel_runs_faster(case):
+    M, N, K, gs, epi, split = case
+    for layer in ("linear", "quantize"):
+        k = q.layer_kernel(M, N, K, gs, layer, epi, split)
+        assert k["kernel"] != "wide" or (layer == "linear" and k["teams"] == 1), (layer, k)
