@@ -7,7 +7,7 @@ namespace quartz {
 namespace {
 
 // Launch times in microseconds, fitted per kind of layer (relative least
-// squares; every tile and the other kernel timed
+// squares; every tile and the other kernel, w4a4_linear or w4a4_gemm, timed
 // over 3200 random shapes of a kind, M to 18432, K to 12288, every G_s, half
 // with a workspace; residuals 2-4 %, 10 % where tiles are fewer than
 // workgroups and split):
@@ -42,11 +42,17 @@ namespace {
 // which its times include: 5823 x 4608 -> 704 stays with w4a4_linear for both
 // outputs (46.9 us against 50.4 for the quantized one).
 //
+// A convolution's other kernel is w4a4_gemm, whose waves all multiply, and
+// whose gather costs less of a tile that is 256 rows high (12540 x 2880 -> 560:
+// 40.8 us against 49.5 for 4 x 32 rows; 4096 x 5760 -> 640: 44 against 37 for
+// two teams, static 41 against 26).
+//
 // The choice takes what is expected to be at least 4 % faster, so that what is
 // not in these terms does not turn it into a loss: over the fitted shapes it is
 // 0.1 to 0.4 % slower than the best kernel and tile (geometric mean), 0.68 to
-// 0.71 of w4a4_linear's time, and slower than the other kernel by
-// more than 2 % in 11 of 12800 shapes.
+// 0.71 of w4a4_linear's time (convolutions 0.50 and 0.43 of
+// w4a4_gemm's), and slower than the other kernel by
+// more than 2 % in 15 of 19200 shapes.
 struct WideCost {
     float c, g0, g1, g8, t0, t1, te, u, s;
 };
@@ -64,7 +70,7 @@ struct Costs {
 // the asymmetric mode's zero-point operands leave no registers for 8 row tiles
 // (20 values spill around every group: 98 us against 69 at 7 x 32 rows, 4608 x
 // 3072 -> 3072)
-constexpr Costs kCosts[4] = {
+constexpr Costs kCosts[6] = {
     // per-group, bf16 output
     {{4.437f, 0.265f, 0.076f, 0.043f, -0.149f, 0.237f, 0.312f, 0.023f, 0.354f},
      {3.426f, 0.293f, 0.072f, 0.064f, 0.396f, 0.386f, 0.181f, 0.020f, 0.098f},
@@ -93,14 +99,22 @@ constexpr Costs kCosts[4] = {
      {6.084f, 0.664f, 0.017f, -0.094f, 0.389f, 1.629f, 0.100f, 2.851f},
      {19.108f, 0.690f, 0.017f, 3.293f, 1.498f},
      {22.105f, 0.733f, 0.048f, 0.0f, 1.198f}},
+    // convolution
+    {{4.838f, 0.331f, 0.086f, 0.031f, -0.778f, 0.165f, 0.331f, 0.005f, 0.697f},
+     {3.176f, 0.413f, 0.064f, 0.049f, 0.094f, 0.424f, 0.197f, 0.010f, 0.410f},
+     {2.984f, 0.525f, 0.0f, 0.077f, 1.575f, 0.0f, 0.145f, 0.023f, 0.0f},
+     {6.197f, 0.548f, 0.109f, 0.0f, 0.815f, 1.688f, 0.030f, 3.478f},
+     {19.050f, 0.630f, 0.089f, 3.129f, -0.348f},
+     {21.668f, 0.732f, 0.101f, 0.0f, 0.417f}},
+    // static convolution
+    {{4.324f, 0.263f, 0.032f, 0.060f, -0.539f, 0.208f, 0.311f, 0.008f, 0.663f},
+     {3.182f, 0.353f, 0.011f, 0.098f, 0.257f, 0.332f, 0.192f, 0.008f, 0.410f},
+     {3.022f, 0.378f, 0.0f, 0.034f, 1.398f, 0.0f, 0.148f, 0.027f, 0.0f},
+     {5.745f, 0.500f, 0.068f, 0.0f, 0.806f, 1.641f, 0.019f, 2.418f},
+     {18.617f, 0.506f, 0.128f, 4.409f, 0.624f},
+     {22.779f, 0.599f, 0.076f, 0.0f, 1.058f}},
 };
 constexpr float kMargin = 0.96f;
-// The per-group convolution takes the tile that the linear layer takes on the
-// im2col matrix (with or without its split, as a workspace is there): both
-// then add the groups in the same order, so their outputs are equal bit for
-// bit.  The static one's sums are exact integers in any order, and its gather
-// weighs more on w4a4_gemm, whose waves all multiply, than on the wide kernel.
-constexpr float kConvStatic = 1.2f;
 
 // the tiles, by teams: one, two, four
 struct Tile {
@@ -134,7 +148,7 @@ struct Best {
 };
 std::array<Best, 3> best_tiles(LayerKind kind, const LayerShape& s, const TileLoads& l)
 {
-    const Costs& k = kCosts[kind == LayerKind::kConv ? 0 : kind == LayerKind::kConvStatic ? 2 : (int)kind];
+    const Costs& k = kCosts[(int)kind];
     std::array<Best, 3> best;
     best.fill({1e30f, {0, 0}});
     for (int i = 0; i < kNumTiles; ++i) {
@@ -157,7 +171,7 @@ std::array<Best, 3> best_tiles(LayerKind kind, const LayerShape& s, const TileLo
 // the other kernel, with its schedule
 float other_us(LayerKind kind, const LayerShape& s, const GemmSchedule& sch)
 {
-    const Costs& k = kCosts[kind == LayerKind::kConv ? 0 : kind == LayerKind::kConvStatic ? 2 : (int)kind];
+    const Costs& k = kCosts[(int)kind];
     const float tiles = (float)(sch.sk_first + sch.sk_tiles), groups = (float)sch.groups, load = tiles / (float)s.blocks;
     const bool fine = s.lzs_group == 8;
     if (sch.sk_tiles == 0) {
@@ -173,13 +187,30 @@ float other_us(LayerKind kind, const LayerShape& s, const GemmSchedule& sch)
 
 }  // namespace
 
-// The linear layer and its quantized output have to add the groups of an output
-// in one order: the codes are those of the stored bf16 output, bit for bit.
-// The orders are ascending (one team, or w4a4_linear without a split), by two
-// teams, by four, and that of w4a4_linear's split.  One that w4a4_linear does
-// not have is open when some tile of it beats w4a4_linear for both outputs
-// (14720 x 512 -> 384: two teams would take 14.3 us for the quantized one
-// against 12.9), and the bf16 output's times pick among the open ones.
+// the tile that beats `limit` by most
+WideShape fastest(const std::array<Best, 3>& b, float limit)
+{
+    WideShape w{0, 0};
+    for (const Best& x : b)
+        if (x.us < limit) {
+            limit = x.us;
+            w = x.w;
+        }
+    return w;
+}
+
+// Each kind of layer decides by its own times, but some have to add the groups
+// of an output in one order, so that their results are equal bit for bit: the
+// quantized output (its codes are those of the stored bf16 output), and a
+// convolution and the linear layer on its im2col matrix when neither's other
+// kernel splits tiles.  The static setting's sums are exact integers in any
+// order up to K = 21376 (|sum| <= 784 K < 2^24), and a layer and its
+// convolution share an order past that.  The orders are ascending (one team,
+// or the other kernel without a split), by two teams, by four, and that of
+// w4a4_linear's split.  One that the other kernels don't have is open when
+// some tile of it beats them for every kind that shares it (14720 x 512 -> 384:
+// two teams would take 14.3 us for the quantized output against 12.9); the
+// bf16 output's times pick among the open ones.
 WideShape wide_shape(LayerKind kind, const LayerShape& s)
 {
     // the kernel's offsets are 32-bit: every array's range ends below 2^30,
@@ -190,23 +221,41 @@ WideShape wide_shape(LayerKind kind, const LayerShape& s)
     if (s.M * G * 32 > kMost || panels * G * kChunkBytes > kMost || s.N * G * 2 > kMost || s.M > (int64_t(1) << 22))
         return {0, 0};
     const TileLoads loads(s);
-    const LayerKind layer = kind == LayerKind::kQuantized || kind == LayerKind::kConv ? LayerKind::kLinear : kind;
+    const bool conv = kind == LayerKind::kConv || kind == LayerKind::kConvStatic;
+    const LayerKind layer = kind == LayerKind::kQuantized || kind == LayerKind::kConv ? LayerKind::kLinear
+                            : kind == LayerKind::kConvStatic                          ? LayerKind::kStatic
+                                                                                      : kind;
     const GemmSchedule lin = linear_schedule(s.M, s.N, s.K, s.blocks, s.split);
     const bool whole = lin.sk_tiles == 0;
+    // the convolution that shares the order, if there is one
+    constexpr int64_t kExactK = (int64_t(1) << 24) / 784;
+    const LayerKind gathered = layer == LayerKind::kStatic ? LayerKind::kConvStatic : LayerKind::kConv;
+    GemmSchedule gemm{};
+    bool tied = s.K % (9 * kGroup) == 0 && layer != LayerKind::kAsym && (layer != LayerKind::kStatic || s.K > kExactK);
+    if (tied || conv)
+        gemm = gemm_schedule(s.M, s.N, s.K, s.blocks, s.split);
+    tied = tied && whole && gemm.sk_tiles == 0;
+
     const std::array<Best, 3> own = best_tiles(kind, s, loads);
-    const float own_other = other_us(kind, s, lin) * (kind == LayerKind::kConvStatic ? kConvStatic : kMargin);
+    const float own_other = kMargin * other_us(kind, s, conv ? gemm : lin);
+    if (conv && !tied)
+        return fastest(own, own_other);
     const std::array<Best, 3> y = kind == layer ? own : best_tiles(layer, s, loads);
     const float y_other = kind == layer ? own_other : kMargin * other_us(layer, s, lin);
     bool open[3];
     for (int c = 0; c < 3; ++c)
         open[c] = y[c].us < y_other;
-    if (layer == LayerKind::kLinear && s.N % kGroup == 0) {
-        const std::array<Best, 3> b = best_tiles(LayerKind::kQuantized, s, loads);
-        const float limit = kMargin * other_us(LayerKind::kQuantized, s, lin);
+    auto shared_with = [&](LayerKind k, const GemmSchedule& sch) {
+        const std::array<Best, 3> b = k == kind ? own : best_tiles(k, s, loads);
+        const float limit = k == kind ? own_other : kMargin * other_us(k, s, sch);
         for (int c = 0; c < 3; ++c)
             open[c] = open[c] && b[c].us < limit;
-    }
-    int order = whole ? 0 : -1;                  // w4a4_linear's
+    };
+    if (layer == LayerKind::kLinear && s.N % kGroup == 0)
+        shared_with(LayerKind::kQuantized, lin);
+    if (tied)
+        shared_with(gathered, gemm);
+    int order = whole ? 0 : -1;                  // the other kernel's
     float best = whole ? std::min(y[0].us, y_other) : y_other;
     for (int c = whole ? 1 : 0; c < 3; ++c)
         if (open[c] && y[c].us < best) {
