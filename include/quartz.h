@@ -191,8 +191,9 @@ quartz_status quartz_w4a4_linear_ws(const uint8_t* codes, const uint8_t* flags,
  *     whose workspace (quartz_w4a4_linear_workspace_bytes) is larger returns
  *     QUARTZ_ERR_WORKSPACE and launches nothing;
  *   - nothing is allocated: no hipMalloc, hipFree or allocating library call;
- *   - each call first clears the counters with a small kernel on `stream`
- *     (no memset node, so the call may be captured into a graph);
+ *   - a call that splits tiles (quartz_w4a4_layer_kernel) first clears the
+ *     counters with a small kernel on `stream` (no memset node, so the call may
+ *     be captured into a graph); the others use neither counters nor slots;
  *   - every call on one GPU shares that GPU's array: calls that overlap in
  *     time on one GPU (two streams, two threads) race and give wrong results.
  * Errors as for quartz_w4a4_linear_ws.

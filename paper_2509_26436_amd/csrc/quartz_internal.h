@@ -198,13 +198,15 @@ hipError_t launch_w4a4_linear_asym(const uint8_t* codes, const uint8_t* flags,
                                    const GemmSchedule& sch, void* workspace, hipStream_t stream);
 
 // `workspace`: gemm_workspace_bytes(sch) bytes whose counter part is zero
-// (left zero again by the launch); unused unless sch.sk_tiles > 0.  With
+// (left zero again by the launch); unused unless sch.sk_tiles > 0 and the
+// layer does not run the wide kernel (wide: wide_shape's answer).  With
 // qout.codes set, y is not written and N % 64 == 0.
 hipError_t launch_w4a4_linear(const uint8_t* codes, const uint8_t* flags,
                               const uint16_t* scales, const uint8_t* w_packed,
                               const uint16_t* bias, uint16_t* y, int64_t M, int64_t N, int64_t K,
                               int64_t ldy, int lzs_group, int epilogue, const GemmSchedule& sch,
-                              void* workspace, const QuantOut& qout, hipStream_t stream);
+                              const WideShape& wide, void* workspace, const QuantOut& qout,
+                              hipStream_t stream);
 
 // The LDM setting: codes and flags of quartz_quantize_act_static, w_packed of
 // the per-channel pack (the channel scale in every group's scale slot).

@@ -108,14 +108,15 @@ hipError_t launch_w4a4_linear(const uint8_t* codes, const uint8_t* flags,
                               const uint16_t* scales, const uint8_t* w_packed,
                               const uint16_t* bias, uint16_t* y, int64_t M, int64_t N, int64_t K,
                               int64_t ldy, int lzs_group, int epilogue, const GemmSchedule& sch,
-                              void* workspace, const QuantOut& qout, hipStream_t stream)
+                              const WideShape& wide, void* workspace, const QuantOut& qout,
+                              hipStream_t stream)
 {
     if (sch.blocks <= 0)
         return hipErrorInvalidConfiguration;
     GemmLaunch a{codes, flags, scales, w_packed, bias, y, nullptr, M, N, K, ldy, lzs_group,
                  epilogue, sch, nullptr, nullptr, qout, 0.0f};
     split_workspace(sch, workspace, a.counters, a.slots);
-    a.wide = layer_tile(qout.codes ? LayerKind::kQuantized : LayerKind::kLinear, a);
+    a.wide = wide;
     return launch_linear(a, stream);
 }
 

@@ -62,3 +62,44 @@ def test_noalloc_equals_workspace_entry_point_twice():
     _noalloc_vs_ws(*big, seed=71)
     _noalloc_vs_ws(*small, seed=72)      # second call, smaller input, same scratch array
     _noalloc_vs_ws(*big, seed=73)        # and the larger shape again after it
+
+
+@pytest.mark.parametrize("M,N,K,epi,kernel,nodes", [
+    (1200, 1000, 3072, 0, "wide", 1),        # nothing split: the counters are not touched
+    (300, 260, 3072, 1, "wide", 1),
+    (1024, 1280, 11520, 0, "linear", 2),     # split: cleared by a kernel first
+])
+def test_noalloc_launches_what_its_kernel_needs(M, N, K, epi, kernel, nodes):
+    """Kernels that a captured call records; its replays, with the scratch array
+    used by another call and the inputs' layer run eagerly between them, give the
+    workspace entry point's output."""
+    import ctypes
+    import torch
+    import paper_2509_26436_amd as q
+    print(f"noalloc graph {M}x{K}->{N}", flush=True)
+    blocks = torch.cuda.get_device_properties(0).multi_processor_count
+    k = q.layer_kernel(M, N, K, 16, "linear", epi, True, blocks)
+    if blocks == 256:
+        assert k["kernel"] == kernel and k["split"] == (nodes == 2), k
+    _, _, _, qa, pw, bias = _case(M, N, K, 16, seed=81)
+    want = q.w4a4_linear(qa, pw, bias, epi, workspace=q.gemm_workspace(M, N, K, "cuda"))
+    _, _, _, qa2, pw2, bias2 = _case(1024, 1280, 11520, 16, seed=82)
+    other = torch.empty((1024, 1280), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    q.w4a4_linear_noalloc(qa, pw, out, bias, epi)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        q.w4a4_linear_noalloc(qa, pw, out, bias, epi)
+    count = ctypes.c_size_t(0)
+    get_nodes = q.load().hipGraphGetNodes    # (of the HIP runtime the library is linked to)
+    get_nodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+    assert get_nodes(graph.raw_cuda_graph(), None, ctypes.addressof(count)) == 0
+    assert count.value == (2 if k["split"] else 1)
+    graph.instantiate()
+    for _ in range(3):
+        out.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        q.w4a4_linear_noalloc(qa2, pw2, other, bias2, 0)
