@@ -75,7 +75,7 @@ def test_weight_group_sums_bit_exact(N, K):
 CASES = [
     # (cfg, layer, M, N, gs, epilogue, bias, workspace)
     (1, 0, 200, 136, 16, 0, True, False),
-    (2, 3, 160, 448, 16, 0, True, True),      # post-GELU input, split along K
+    (2, 3, 160, 448, 16, 0, True, True),      # post-GELU input
     (3, 0, 300, 200, 8, 1, False, True),      # ragged, GELU, no bias
     (5, 0, 257, 320, 64, 1, True, False),     # post-SiLU im2col input
     (3, 3, 64, 129, 32, 0, True, True),       # K = 12288
@@ -121,9 +121,9 @@ def _sample(n: int, count: int, seed: int, tile: int) -> np.ndarray:
 @pytest.mark.parametrize("layer", [0, 3], ids=["qkv", "fc2"])
 def test_asym_full_size_flux(layer):
     """A FLUX block layer at full size through the workspace entry point, the
-    launch the bench times (qkv splits its last round along K, fc2 every tile):
-    the quantizer bit for bit and the outputs within tolerance on a sampled
-    grid of rows (tiles of 128) and columns (tiles of 256)."""
+    launch the bench times (the wide kernel's tiles of 224 x 256): the quantizer
+    bit for bit and the outputs within tolerance on a sampled grid of rows and
+    columns."""
     import torch
     q = _q()
     L = W.CONFIGS[3].layers[layer]

@@ -5,12 +5,14 @@ oracle's layer on the im2col matrix built on the host (within the output
 tolerance of tests/helpers.py), and bit for bit against the GPU's explicit
 path on that same im2col matrix (quantizer + linear entry point), which by the
 reading the host tests pin computes the same codes.  The bit for bit
-comparison is between calls without the stream-K split: the linear entry
-point runs tiles of another shape, so a split adds its partial sums in
-another order; split calls are held to the oracle tolerance.  Ragged images (rows ending inside a tile), several images, C from 64
-to 320 (one to five channel blocks), every G_s, GELU, bias, the stream-K
-split, a strided output with guard rows, and the config-5 layers at full size
-(sampled rows against the oracle)."""
+comparison is between calls without a workspace: where the kernels split
+their tiles along K, those of the linear entry point have another shape, so
+the partial sums are added in another order; calls with a workspace are held
+to the oracle tolerance.  Ragged images (rows ending inside a tile), several
+images, C from 64 to 320 (one to five channel blocks), every G_s, GELU, bias, a
+strided output with guard rows, and the config-5 layers at full size (sampled
+rows against the oracle).  The small ones run the wide kernel;
+test_gpu_other_kernels.py covers w4a4_gemm and its split."""
 import numpy as np
 import pytest
 

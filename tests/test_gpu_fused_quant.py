@@ -32,11 +32,11 @@ def _q():
     return q
 
 
-def _split_of(M, N, K):
+def _assert_launches(M, N, K, gs, split):
     import torch
-    q = _q()
-    blocks = torch.cuda.get_device_properties(0).multi_processor_count
-    return q.linear_schedule(M, N, K, blocks)[0]["split"]
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        k = _q().layer_kernel(M, N, K, gs, "quantize", 0, True)
+        assert (k["kernel"], k["split"]) == (("linear", True) if split else ("wide", False)), k
 
 
 def _host(qa):
@@ -61,28 +61,39 @@ def _fused(xb, wb, bias_b, gs, ogs, epi, use_ws, zeros=False):
 EXACT = [
     # (M, N, K, gs, out_gs, bias, workspace, zeros)
     (300, 320, 256, 16, 16, True, False, True),     # ragged M, half-used last column tile
-    (300, 320, 2048, 8, 32, True, True, False),     # split along K (tiles shared)
+    (300, 320, 2048, 8, 32, True, True, False),
     (64, 64, 128, 64, 8, False, False, False),      # one wave column
-    (1, 128, 2048, 32, 64, True, True, False),      # a single row, one tile over 2 workgroups
-    (513, 448, 2048, 16, 16, True, True, True),     # three tile rows, split
+    (1, 128, 2048, 32, 64, True, True, False),      # a single row
+    (513, 448, 2048, 16, 16, True, True, True),     # ragged rows in every tile row
     (256, 1152, 512, 16, 16, True, False, False),   # the single-linear width
+]
+# the same with w4a4_linear's tiles split along K (the wide kernel runs those above)
+EXACT_SPLIT = [
+    (359, 2816, 8128, 8, 16, True, True, True),
+    (333, 3008, 11712, 16, 64, True, True, False),
+    (396, 2496, 11968, 64, 8, False, True, False),
 ]
 
 
-@pytest.mark.parametrize("case", EXACT, ids=lambda c: f"{c[0]}x{c[1]}x{c[2]}-gs{c[3]}-o{c[4]}"
+@pytest.mark.parametrize("case", EXACT + EXACT_SPLIT, ids=lambda c: f"{c[0]}x{c[1]}x{c[2]}-gs{c[3]}-o{c[4]}"
                          f"{'-ws' if c[6] else ''}")
 def test_exact_inputs_bit_exact(case):
     M, N, K, gs, ogs, with_bias, use_ws, zeros = case
     print(f"fused quantize exact M={M} N={N} K={K} gs={gs} out_gs={ogs} ws={use_ws}", flush=True)
+    split = case in EXACT_SPLIT
     if use_ws:
-        assert _split_of(M, N, K) == 1
+        _assert_launches(M, N, K, gs, split)
     c = W.make_exact_case(7000 + M + N + K, M, N, K)
     bias_b = c.bias if with_bias else None
     _, _, _, _, out = _fused(c.x, c.w, bias_b, gs, ogs, 0, use_ws, zeros)
-    a_ref = oracle.quantize_act(c.x, gs)
+    codes, flags, scales, z = _host(out)
+    x = c.x
+    if split:                                       # sampled rows (the outputs of a row are its own)
+        rows = np.unique(np.r_[0, 63, 64, 127, 128, M - 1, np.linspace(0, M - 1, 20).astype(int)])
+        x, codes, flags, scales = x[rows], codes[:, rows], flags[:, rows], scales[:, rows]
+    a_ref = oracle.quantize_act(x, gs)
     wq, sw = oracle.quantize_weight(c.w)
     ref = oracle.linear_quantize(a_ref, wq, sw, bias_b, 0, ogs)
-    codes, flags, scales, z = _host(out)
     np.testing.assert_array_equal(scales, ref.abi_scales)
     np.testing.assert_array_equal(flags, ref.abi_flags)
     np.testing.assert_array_equal(codes, ref.codes)
@@ -145,7 +156,7 @@ def _check_admissible(out, y64, S, K, gelu, ogs):
 
 REAL = [
     # (cfg, layer, M, N, gs, out_gs, epilogue, workspace)
-    (3, 2, 300, 1152, 16, 16, 1, True),     # FLUX fc1 rows, GELU, split
+    (3, 2, 300, 1152, 16, 16, 1, True),     # FLUX fc1 rows, GELU
     (2, 2, 257, 1216, 8, 32, 1, False),     # PixArt fc1 rows, ragged M, half tile
     (1, 0, 96, 640, 32, 8, 0, True),        # single linear, no activation
 ]

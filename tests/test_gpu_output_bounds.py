@@ -5,7 +5,8 @@ must equal the output of the same call into a fresh tensor.  M is chosen so
 that the last tile row ends inside a wave's 64 rows (M % 64 != 0), which is
 where a store whose row offset escaped the bounds check would land in the
 guard rows; with and without the stream-K workspace, bias and GELU, per-group,
-static (LDM) and asymmetric modes."""
+static (LDM) and asymmetric modes.  (These sizes run the wide kernel;
+test_gpu_other_kernels.py holds the same for the kernels beside it.)"""
 import numpy as np
 import pytest
 
@@ -45,7 +46,7 @@ SHAPES = [
     (200, 136, 192, 16, 0, True, False, 0),
     (37, 64, 128, 8, 1, True, False, 6),
     (1, 128, 64, 64, 0, False, False, 0),
-    (257, 129, 1152, 32, 0, True, True, 0),     # two tiles split along K
+    (257, 129, 1152, 32, 0, True, True, 0),
     (130, 320, 576, 16, 1, False, True, 4),
 ]
 

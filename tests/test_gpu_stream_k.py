@@ -1,12 +1,14 @@
 """GPU parity of the workspace (stream-K) entry point quartz_w4a4_linear_ws.
 
-Shapes are chosen so that, on a device with 256 compute units, the schedule
-splits tiles along K: fewer tiles than workgroups (tiles shared by up to eight
-workgroups), a ragged number of rounds, every LZS subgroup size, GELU, no
-bias and a strided output.  Every output is compared with the oracle within
-the tolerance of tests/helpers.py; repeated calls on one workspace must give
-bit-identical outputs (the counters are reset, the summation order is fixed);
-garbage in the slot part of the workspace must not matter.
+The first shapes are small ones whose schedule would split but which the wide
+kernel runs, with the workspace at hand: ragged rows and columns, every LZS
+subgroup size, GELU, no bias and a strided output, every output compared with
+the oracle within the tolerance of tests/helpers.py.  The others launch the
+split (asserted through the library's query on a device with 256 compute
+units), which all the modes' split cases of test_gpu_other_kernels.py cover
+further: repeated calls on one workspace must give bit-identical outputs (the
+counters are reset, the summation order is fixed); garbage in the slot part of
+the workspace must not matter.
 """
 import numpy as np
 import pytest
@@ -56,14 +58,21 @@ def _schedule_of(M, N, K):
     return q.linear_schedule(M, N, K, blocks)[0]
 
 
+def _assert_launches(M, N, K, gs, epi, kernel, split):
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        k = _q().layer_kernel(M, N, K, gs, "linear", epi, True)
+        assert (k["kernel"], k["split"]) == (kernel, split), k
+
+
 CASES = [
-    # (cfg, layer, M, N, gs, epilogue, bias, ldy_pad); tiles of 128 x 256
-    (2, 3, 160, 448, 16, 0, True, 0),      # 4 tiles x 72 groups over 18 workgroups
-    (2, 3, 70, 130, 16, 1, False, 0),      # 1 tile x 72 groups over 4 workgroups, GELU, no bias
+    # (cfg, layer, M, N, gs, epilogue, bias, ldy_pad)
+    (2, 3, 160, 448, 16, 0, True, 0),      # 72 groups
+    (2, 3, 70, 130, 16, 1, False, 0),      # GELU, no bias
     (3, 0, 300, 200, 8, 0, True, 6),       # ragged rows and columns, strided output
-    (3, 3, 257, 129, 32, 0, True, 0),      # K = 12288: 3 tiles x 192 groups
-    (5, 0, 513, 320, 64, 1, True, 0),      # 10 tiles, GELU
-    (2, 3, 64, 1152, 16, 0, True, 0),      # one tile row, 5 tiles x 72 groups
+    (3, 3, 257, 129, 32, 0, True, 0),      # K = 12288: 192 groups
+    (5, 0, 513, 320, 64, 1, True, 0),      # GELU
+    (2, 3, 64, 1152, 16, 0, True, 0),      # one tile row
 ]
 
 
@@ -75,8 +84,7 @@ def test_ws_linear_parity(case):
     L = W.CONFIGS[cfg].layers[layer]
     K = L.K
     print(f"stream-K parity cfg={cfg} layer={layer} M={M} N={N} K={K} gs={gs}", flush=True)
-    sched = _schedule_of(M, N, K)
-    assert sched["split"] == 1, sched
+    _assert_launches(M, N, K, gs, epi, "wide", False)
     xb = W.make_x(cfg, layer, rows=M)
     wb = W.make_w(cfg, layer, rows=N)
     bias = W.make_bias(cfg, layer, cols=N) if with_bias else None
@@ -85,9 +93,32 @@ def test_ws_linear_parity(case):
     assert ws is not None
     y1 = _ws_linear(qa, pw, bias, epi, ws, ldy_pad)
     _check(y1, a_ref, wq_ref, sw_ref, bias, epi, K)
-    # the counters were reset: a second call on the same workspace gives the same bits
+    # a second call on the same workspace gives the same bits
     y2 = _ws_linear(qa, pw, bias, epi, ws, ldy_pad)
     assert torch.equal(y1.view(torch.int16), y2.view(torch.int16))
+
+
+SPLIT = (836, 1166, 9600)      # 35 tiles of 128 x 256 by 150 groups
+
+
+def _split_case(gs):
+    """Quantized activations, packed weight, bias bits and a check of sampled outputs."""
+    M, N, K = SPLIT
+    xb = W.make_random_x(91, M, K, "t3", 0.05)
+    rng = np.random.Generator(np.random.PCG64(92))
+    wb = W.to_bf16_bits(rng.normal(0, 0.02, (N, K)))
+    bias = W.to_bf16_bits(rng.normal(0, 0.02, N))
+    q = _q()
+    rows = np.unique(np.concatenate([[0, 127, 128, M - 1], rng.choice(M, 40, replace=False)]))
+    cols = np.unique(np.concatenate([[0, 255, 256, N - 1], rng.choice(N, 60, replace=False)]))
+    y64, S = oracle.linear_f64(oracle.quantize_act(xb[rows], gs), *oracle.quantize_weight(wb[cols]), bias[cols],
+                               epilogue=0)
+
+    def check(y):
+        got = bf16_bits_to_f64(to_host_u16(y[rows.tolist()][:, cols.tolist()].contiguous()))
+        err, tol = np.abs(got - y64), y_tolerance(y64, S, K)
+        assert (err <= tol).all(), f"worst excess {(err - tol).max():.3e}"
+    return q.quantize_act(to_dev_bf16(xb), gs), q.pack_weight(to_dev_bf16(wb)), bias, check
 
 
 def test_ws_slot_contents_do_not_matter():
@@ -95,35 +126,29 @@ def test_ws_slot_contents_do_not_matter():
     (NaN floats) and the result is unchanged."""
     import torch
     q = _q()
-    M, N, K = 160, 448, 4608
-    xb = W.make_x(2, 3, rows=M)
-    wb = W.make_w(2, 3, rows=N)
-    bias = W.make_bias(2, 3, cols=N)
-    qa, pw, a_ref, wq_ref, sw_ref = _gemm_case(xb, wb, 16)
+    M, N, K = SPLIT
+    _assert_launches(M, N, K, 16, 0, "linear", True)
+    qa, pw, bias, check = _split_case(16)
     ws = q.gemm_workspace(M, N, K, "cuda")
     y1 = _ws_linear(qa, pw, bias, 0, ws)
     sched = _schedule_of(M, N, K)
     counter_bytes = -(-sched["sk_tiles"] * 8 * 4 // 256) * 256
+    assert not ws[:counter_bytes].any() and ws[counter_bytes:].any()   # counters reset, slots written
     ws[counter_bytes:] = 0xFF
     y2 = _ws_linear(qa, pw, bias, 0, ws)
     assert torch.equal(y1.view(torch.int16), y2.view(torch.int16))
-    _check(y2, a_ref, wq_ref, sw_ref, bias, 0, K)
+    check(y2)
 
 
 def test_ws_matches_plain_entry_point_within_order():
     """The workspace path and the whole-tile path differ only in the fp32 order
     of the group sum: both within tolerance, and within a few bf16 ulps."""
     q = _q()
-    M, N = 300, 200
-    L = W.CONFIGS[3].layers[3]
-    xb = W.make_x(3, 3, rows=M)
-    wb = W.make_w(3, 3, rows=N)
-    bias = W.make_bias(3, 3, cols=N)
-    qa, pw, a_ref, wq_ref, sw_ref = _gemm_case(xb, wb, 16)
-    y_plain = q.w4a4_linear(qa, pw, to_dev_bf16(bias), 0)
-    y_ws = _ws_linear(qa, pw, bias, 0, q.gemm_workspace(M, N, L.K, "cuda"))
-    _check(y_plain, a_ref, wq_ref, sw_ref, bias, 0, L.K)
-    _check(y_ws, a_ref, wq_ref, sw_ref, bias, 0, L.K)
+    M, N, K = SPLIT
+    _assert_launches(M, N, K, 16, 0, "linear", True)
+    qa, pw, bias, check = _split_case(16)
+    check(q.w4a4_linear(qa, pw, to_dev_bf16(bias), 0))
+    check(_ws_linear(qa, pw, bias, 0, q.gemm_workspace(M, N, K, "cuda")))
 
 
 def test_ws_null_and_too_small():
