@@ -151,8 +151,10 @@ quartz_status quartz_w4a4_linear(const uint8_t* codes, const uint8_t* flags,
  * becomes persistent and the tiles of the last rounds are cut along K
  * (stream-K); a tile shared by several workgroups gets their fp32 partial
  * sums added in a fixed order by the last one to finish, so results are
- * deterministic.  The values are those of quartz_w4a4_linear up to the fp32
- * summation order over groups (Section 4.4 fixes no order).
+ * deterministic.  Shapes for which whole tiles of another size are faster run
+ * those and leave the workspace alone (quartz_w4a4_layer_kernel tells).  The
+ * values are those of quartz_w4a4_linear up to the fp32 summation order over
+ * groups (Section 4.4 fixes no order).
  *
  *   workspace        device memory, 16-byte aligned, at least
  *                    quartz_w4a4_linear_workspace_bytes(M, N, K, 64) bytes,
@@ -168,6 +170,8 @@ quartz_status quartz_w4a4_linear(const uint8_t* codes, const uint8_t* flags,
  * quartz_w4a4_linear_workspace_bytes: the size for this M, N, K on the
  * current device (it depends on its number of compute units); 0 when the
  * tiles fill whole rounds (then NULL may be passed) or the sizes are invalid.
+ * It serves every layer and both convolutions of these sizes, and a smaller
+ * workspace is refused also where the call would not touch it.
  */
 size_t quartz_w4a4_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int32_t group_size);
 
@@ -351,8 +355,13 @@ quartz_status quartz_w4a4_gemm_i32(const uint8_t* codes, const uint8_t* flags,
  * channels of one input pixel (or zero padding), and a group's scale, FLAGs
  * and codes depend on its 64 values only, so quantizing the feature map
  * once gives the codes of every im2col row; the GEMM reads them at the
- * pixel each tap points to.  The result equals quartz_w4a4_linear_ws (or
- * quartz_w4a4_linear_static) on the quantized im2col matrix, bit for bit.
+ * pixel each tap points to.  Without a workspace the result equals the linear
+ * layer's (quartz_w4a4_linear, or quartz_w4a4_linear_static) on the quantized
+ * im2col matrix, bit for bit; with one in both calls it does so unless the
+ * schedule of either kernel splits tiles (quartz_w4a4_linear_schedule, tiles
+ * of 128 x 256 and of 256 x 128), when the two may add an output's groups in
+ * different orders (the static setting's sums are exact in any order up to
+ * K = 21376).
  *
  * quartz_w4a4_conv3x3: the per-group setting.
  *   codes, flags, scales  outputs of quartz_quantize_act for the feature map
@@ -370,7 +379,7 @@ quartz_status quartz_w4a4_gemm_i32(const uint8_t* codes, const uint8_t* flags,
  *   quartz_quantize_act_static for the feature map with act_scale, w_packed
  *   of quartz_pack_weight_per_channel for the weight [N][9 C]; otherwise as
  *   quartz_w4a4_conv3x3 (equal to quartz_w4a4_linear_static on the im2col
- *   matrix).
+ *   matrix, as said above).
  */
 quartz_status quartz_w4a4_conv3x3(const uint8_t* codes, const uint8_t* flags,
                                   const uint16_t* scales, const void* w_packed,

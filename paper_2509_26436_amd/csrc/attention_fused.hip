@@ -233,7 +233,7 @@ struct AttnStage {
 // [L][ldo], head h at columns h d ...
 //
 // What bounds it is the issue of vector instructions (per 64-key chunk and
-// wave 24 MFMAs at d = 128 beside ~520, 64 of them exponentials), so both
+// wave 24 MFMAs at d = 128 beside 582, counted; 64 are exponentials), so both
 // passes are written as slots: a slot issues the matrix product of one unit
 // (32 rows by 32 queries of one 64-group, with the outer product of its
 // scales) and multiplies out the unit before it, whose product ran meanwhile,
@@ -243,10 +243,10 @@ struct AttnStage {
 // 4608, d = 128 the kernel took 757 us as one chain of scores, softmax,
 // quantizer and PV with a maximum per chunk; 623 in slots, 543 with the
 // swizzled staging, 450 with teams for the last quarter of a round (vector
-// instructions then issue in 77 % of the cycles, MFMAs in 33 %).  Tried and
-// dropped: log2(e) / sqrt(d) folded into the score scales (one instruction
-// less per score and pass, 1-5 % faster, but a larger error: 1.682e-3 against
-// 1.670e-3 of the output's norm).
+// instructions then issue in 80 % of the whole rounds' cycles, MFMAs in 35 %).
+// Tried and dropped: log2(e) / sqrt(d) folded into the score scales (one
+// instruction less per score and pass, 1-5 % faster, but a larger error:
+// 1.682e-3 against 1.670e-3 of the output's norm).
 template <int GS, int G, int WQ, int S>
 __global__ __launch_bounds__(64 * WQ * S) __attribute__((amdgpu_waves_per_eu(2, 2))) void lzs_attention_fused_kernel(
     const uint8_t* __restrict__ qx, const uint16_t* __restrict__ qs,

@@ -213,9 +213,12 @@ WideShape fastest(const std::array<Best, 3>& b, float limit)
 // bf16 output's times pick among the open ones.
 WideShape wide_shape(LayerKind kind, const LayerShape& s)
 {
-    // the kernel's offsets are 32-bit: every array's range ends below 2^30,
-    // where a group past the last one reads, and the rows' offsets of the up
-    // to 7 groups past the last one below 2^31, which marks a lane as outside
+    // the kernel's offsets are 32-bit.  Every array's range ends at 2^30 at
+    // most, where the weights of a group past the last one are read, and an
+    // offset from 2^31 on marks a lane as outside: scalar and lane offsets of
+    // the weights, scales and sums add up to less than 2^32.  So do the rows'
+    // (the fetch runs up to 22 groups past the last one: 2^30 + 22 x 32 x 2^22),
+    // but for waves without rows of their own, which stage what nobody reads.
     constexpr int64_t kMost = int64_t(1) << 30;
     const int64_t G = s.K / kGroup, panels = (s.N + kPanel - 1) / kPanel;
     if (s.M * G * 32 > kMost || panels * G * kChunkBytes > kMost || s.N * G * 2 > kMost || s.M > (int64_t(1) << 22))
